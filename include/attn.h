@@ -258,7 +258,9 @@ size_t attn_unfused_workspace_bytes(int B, int H, int L, int dtype);
  * row over up to the 4 waves of a workgroup (their running maximum and
  * denominator merged with the associative operator) until the grid reaches
  * the CU count.  A row segment that fits the resident tiles is read from HBM
- * once, else twice. */
+ * once, else twice.  attn_softmax runs rows of more than 131072 elements on
+ * these tiles; shorter rows fit the registers of 16 to 1024 threads and are
+ * always read once, as one launch of more, smaller workgroups. */
 typedef struct {
   int32_t feasible;
   int32_t tile_elems;       /* elements one wave moves per tile */
@@ -286,8 +288,7 @@ int attn_softmax_derive(const attn_hw_desc_t* hw, int64_t rows, int64_t n, int e
  * rounded to nearest-even.  causal != 0 treats X as square n x n blocks stacked
  * along the rows and gives column j > (i mod n) of row i weight 0 (the
  * top-left mask of attention scores).  Y may equal X.  Pointers need 2-byte
- * alignment; with n % 8 == 0 and 16-byte aligned X and Y every access is a
- * 16-byte one.  rows >= 1, 1 <= n <= 2^31.  Asynchronous on `stream`. */
+ * alignment.  rows >= 1, 1 <= n <= 2^31.  Asynchronous on `stream`. */
 int attn_softmax(const void* X, void* Y, int64_t rows, int64_t n, int causal, int dtype, void* stream);
 
 /* GEMM C = A B (Section 4's worked example, Figure 1): workgroup tile

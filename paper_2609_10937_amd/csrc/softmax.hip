@@ -1,17 +1,18 @@
-// Row softmax with the online algorithm of Section 5.3, as a standalone
-// operator: Y = softmax(X) along each row of a rows x n matrix.
+// Row softmax (Section 5.3) as a standalone operator: Y = softmax(X) along each
+// row of a rows x n matrix.
 //
-// A wave owns one segment of a row (the CU rule splits a row over up to the
-// workgroup's waves; their partial statistics are merged with the operator
-// of Section 5.3 through LDS).  The segment is read in tiles of one 16-byte
-// load per lane (64 lanes x 8 elements): for every tile the lane's running
-// maximum m and denominator d take the correction exp(m - m_new) and the
-// tile's exponentials; the first MAXT tiles stay in registers (packed 16-bit),
-// so a segment of up to MAXT tiles is read from HBM once, and longer ones are
-// read again for the output.  Elements past the segment, or above the
-// diagonal when causal, enter as -inf (the padding rule of Section 5.3).
-// The 64 lanes' (m, d) pairs and then the segments' are merged with the same
-// operator, and the output pass writes exp(x - m) / d in the input type.
+// Rows of up to 131072 elements stay in the registers of the threads that share
+// them (softmax_rows_kernel).  Longer ones take the online algorithm of Section
+// 5.3 (softmax_kernel): a wave owns one segment of a row (the CU rule splits a
+// row over up to the workgroup's waves; their partial statistics are merged
+// with the operator of Section 5.3 through LDS).  The segment is read in tiles
+// of one 16-byte load per lane (64 lanes x 8 elements): for every tile the
+// lane's running maximum m and denominator d take the correction exp(m - m_new)
+// and the tile's exponentials; the first MAXT tiles stay in registers (packed
+// 16-bit), the others are read again for the output.  Elements past the segment,
+// or above the diagonal when causal, enter as -inf (the padding rule of Section
+// 5.3).  The 64 lanes' (m, d) pairs and then the segments' are merged with the
+// same operator, and the output pass writes exp(x - m) / d in the input type.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -22,6 +23,9 @@ namespace attn {
 namespace {
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+// 16 bytes at any element boundary: gfx950 serves global accesses of this
+// width at 2-byte alignment, so rows of any length take them.
+typedef uint32_t u32x4_a2_t __attribute__((ext_vector_type(4), aligned(2)));
 
 template <int DT>
 struct Elem;
@@ -59,12 +63,173 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
   return (uint32_t)__builtin_bit_cast(uint16_t, (S)a) | ((uint32_t)__builtin_bit_cast(uint16_t, (S)b) << 16);
 }
 
+// Two 16-bit -inf values packed in a 32-bit word.
+template <int DT>
+constexpr uint32_t kNegInf2 = DT == ATTN_BF16 ? 0xFF80FF80u : 0xFC00FC00u;
+
+// The 8 elements from x[col] on as packed words; elements at or past `end`
+// read as -inf and touch no memory.
+// STREAM: non-temporal loads.
+template <int DT, bool STREAM = false>
+__device__ __forceinline__ u32x4_t load8(const uint16_t* x, int64_t col, int64_t end) {
+  if (col + 8 <= end) {
+    const u32x4_a2_t* a = reinterpret_cast<const u32x4_a2_t*>(x + col);
+    if constexpr (STREAM) return __builtin_nontemporal_load(a);
+    else return *a;
+  }
+  u32x4_t v = {kNegInf2<DT>, kNegInf2<DT>, kNegInf2<DT>, kNegInf2<DT>};
+  if (col < end) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (col + e < end) {
+        const uint32_t h = x[col + e];
+        v[e >> 1] = (e & 1) ? (v[e >> 1] & 0xFFFFu) | (h << 16) : (v[e >> 1] & 0xFFFF0000u) | h;
+      }
+  }
+  return v;
+}
+
+// Store 8 packed elements to y[col] on, as far as `end`.  The output is not
+// read again here: streaming (non-temporal) stores.
+__device__ __forceinline__ void store8(uint16_t* y, int64_t col, int64_t end, const u32x4_t& v) {
+  if (col + 8 <= end) {
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4_a2_t*>(y + col));
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (col + e < end) y[col + e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+  }
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+// Maximum or sum over groups of 16 or 64 lanes, in every lane of the group
+// (lane permutes of the vector unit; no LDS round trip).
+template <int LANES, typename Op>
+__device__ __forceinline__ float lane_reduce(float x, Op op) {
+  static_assert(LANES == 16 || LANES == 64, "lane group");
+  x = op(x, dpp<0xB1>(x));   // lane ^ 1
+  x = op(x, dpp<0x4E>(x));   // lane ^ 2
+  x = op(x, dpp<0x141>(x));  // mirror within 8
+  x = op(x, dpp<0x140>(x));  // mirror within 16
+  if constexpr (LANES == 64) {
+    uint32_t u = __builtin_bit_cast(uint32_t, x);
+    const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    x = op(__builtin_bit_cast(float, (uint32_t)a[0]), __builtin_bit_cast(float, (uint32_t)a[1]));
+    u = __builtin_bit_cast(uint32_t, x);
+    const auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    x = op(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
+  }
+  return x;
+}
+
 }  // namespace
+
+// Rows that fit the registers of their threads: G threads share a row (16 or
+// 64 lanes of a wave, or a workgroup of 256 or 1024), each holding T chunks of
+// 8 elements, chunk t of thread i at column 8 (t G + i).  Every element is
+// read once, as 16-byte accesses at any alignment, all of a thread's loads in
+// flight together; the maximum and then the sum are reduced over the row's
+// threads, and the exponentials stay in registers until they are scaled and
+// written.  Columns above the causal diagonal are not read.  Bound by memory:
+// a row takes the fewest threads whose registers hold it, which keeps many rows
+// in flight per CU and the registers per thread few.  Measured against one wave
+// per row with up to 32 chunks of 512 in registers, bf16 (us): 65536 x 512 73.9
+// -> 21.0 (6.4 TB/s), 32768 x 4096 100.6 -> 78.9, 8192 x 16384 99.0 -> 79.7,
+// 2048 x 65536 140 -> 95.6, 16384 x 16384 200 -> 178; rows of odd length, which
+// were read and written element by element: 65504 x 2049 524 -> 86 us.
+template <int DT, int G, int T, bool STREAM>
+__global__ void __launch_bounds__(G < 256 ? 256 : G) softmax_rows_kernel(const SoftmaxParams p) {
+  constexpr int BT = G < 256 ? 256 : G, R = BT / G;
+  constexpr int NWR = G / 64;  // waves per row (G >= 256)
+  __shared__ float part[2][G >= 256 ? NWR : 1];
+  const int tid = threadIdx.x, lg = tid % G;
+  uint32_t sub = tid / G;
+  if constexpr (G >= 64) sub = __builtin_amdgcn_readfirstlane(sub);
+  const int64_t row = (int64_t)blockIdx.x * R + sub;
+  const bool live = R == 1 || row < p.rows;
+  const int n = (int)p.n;
+  int end = 0;  // end of the visible columns
+  if (live) {
+    end = n;
+    if (p.causal)
+      end = (p.rows <= (int64_t)0xFFFFFFFF ? (int)((uint32_t)row % (uint32_t)n) : (int)(row % n)) + 1;
+  }
+  const uint16_t* x = static_cast<const uint16_t*>(p.x) + (live ? row : 0) * n;
+  uint16_t* y = static_cast<uint16_t*>(p.y) + (live ? row : 0) * n;
+
+  u32x4_t v[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) v[t] = load8<DT, STREAM>(x, 8 * (t * G + lg), end);
+
+  auto vmax = [](float a, float b) { return fmaxf(a, b); };
+  auto vadd = [](float a, float b) { return a + b; };
+  // Reduction over the row's threads.
+  auto reduce = [&](float r, auto op, int slot) {
+    r = lane_reduce<(G < 64 ? 16 : 64)>(r, op);
+    if constexpr (G >= 256) {
+      if ((tid & 63) == 0) part[slot][tid >> 6] = r;
+      __syncthreads();
+      r = part[slot][0];
+#pragma unroll
+      for (int i = 1; i < NWR; ++i) r = op(r, part[slot][i]);
+    }
+    return r;
+  };
+  // Up to 8 chunks the exponentials stay in registers; 16 chunks form them
+  // twice from the packed elements.
+  constexpr bool KEEP = T <= 8;
+  float f[KEEP ? T : 1][8];
+  float m = -INFINITY;
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) m = fmaxf(m, to_f32<DT>(v[t][e >> 1], e & 1));
+  m = reduce(m, vmax, 0);
+  if (m == -INFINITY) m = 0.f;  // a row without finite entries: all weights 0
+  // 16 chunks: opaque between the passes, so that each unpacks them again.
+  auto forget = [&]() {
+    if constexpr (!KEEP) {
+#pragma unroll
+      for (int t = 0; t < T; ++t) asm volatile("" : "+v"(v[t]));
+    }
+  };
+  forget();
+  float d = 0.f;
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float w = exp2_hw((to_f32<DT>(v[t][e >> 1], e & 1) - m) * kLog2e);
+      if constexpr (KEEP) f[t][e] = w;
+      d += w;
+    }
+  d = reduce(d, vadd, 1);
+  const float inv = d > 0.f ? 1.f / d : 0.f;
+  if (!live) return;
+  forget();
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int col = 8 * (t * G + lg);
+    if (col >= n) continue;
+    float w[8];
+    u32x4_t o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if constexpr (KEEP) w[e] = f[t][e];
+      else w[e] = exp2_hw((to_f32<DT>(v[t][e >> 1], e & 1) - m) * kLog2e);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) o[e >> 1] = pack2<DT>(w[e] * inv, w[e + 1] * inv);
+    store8(y, col, n, o);
+  }
+}
 
 // One workgroup of W waves; waves w and the S - 1 after it (S = p.split)
 // share row blockIdx.x * (W / S) + w / S.  ALIGNED: n % 8 == 0 and 16-byte
-// aligned bases, so every lane's 8 elements are one 16-byte access; otherwise
-// elements are loaded and stored one by one.
+// aligned bases, so no chunk of 8 elements crosses the row's end.
 template <int DT, int W, int MAXT, bool ALIGNED>
 __global__ void __launch_bounds__(W * 64) softmax_kernel(const SoftmaxParams p) {
   __shared__ float2 part[W];
@@ -91,11 +256,7 @@ __global__ void __launch_bounds__(W * 64) softmax_kernel(const SoftmaxParams p) 
       v = (u32x4_t){0u, 0u, 0u, 0u};
       if (col < c1) v = *reinterpret_cast<const u32x4_t*>(x + col);
     } else {
-      uint32_t wv[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (col + e < c1) wv[e >> 1] |= (uint32_t)x[col + e] << (16 * (e & 1));
-      v = (u32x4_t){wv[0], wv[1], wv[2], wv[3]};
+      v = load8<DT>(x, col, c1);
     }
   };
   // values of tile t; columns past the segment or above the diagonal -inf
@@ -164,14 +325,9 @@ __global__ void __launch_bounds__(W * 64) softmax_kernel(const SoftmaxParams p) 
     for (int e = 0; e < 8; e += 2)
       o[e >> 1] = pack2<DT>(exp2_hw(__builtin_fmaf(f[e], kLog2e, -ref)) * inv,
                             exp2_hw(__builtin_fmaf(f[e + 1], kLog2e, -ref)) * inv);
-    if constexpr (ALIGNED) {
-      // The output is not read again here: a streaming (non-temporal) store.
-      __builtin_nontemporal_store((u32x4_t){o[0], o[1], o[2], o[3]}, reinterpret_cast<u32x4_t*>(y + col));
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (col + e < c1) y[col + e] = (uint16_t)(o[e >> 1] >> (16 * (e & 1)));
-    }
+    const u32x4_t w = {o[0], o[1], o[2], o[3]};
+    if constexpr (ALIGNED) __builtin_nontemporal_store(w, reinterpret_cast<u32x4_t*>(y + col));
+    else store8(y, col, c1, w);
   };
 #pragma unroll
   for (int t = 0; t < MAXT; ++t)
@@ -183,8 +339,51 @@ __global__ void __launch_bounds__(W * 64) softmax_kernel(const SoftmaxParams p) 
   }
 }
 
+template <int DT, int G, int T>
+static bool launch_rows(const SoftmaxParams& p, bool stream, hipStream_t s) {
+  constexpr int BT = G < 256 ? 256 : G, R = BT / G;
+  const int64_t grid = (p.rows + R - 1) / R;
+  if (grid * BT > 0xFFFFFFFFLL) return false;  // more threads than one launch takes
+  if constexpr (T >= 4) {
+    if (stream) {
+      hipLaunchKernelGGL((softmax_rows_kernel<DT, G, T, true>), dim3((unsigned)grid), dim3(BT), 0, s, p);
+      return true;
+    }
+  }
+  hipLaunchKernelGGL((softmax_rows_kernel<DT, G, T, false>), dim3((unsigned)grid), dim3(BT), 0, s, p);
+  return true;
+}
+
+// Threads per row and chunks per thread of a row of n elements: the fewest
+// threads of 16, 64, 256 and 1024 that hold it in at most 2, 8, 8 and 16 chunks
+// each.  False past that (131072 elements): rows are then read twice.
+// Inputs above the 256 MiB of the memory-side cache are read with non-temporal
+// loads (bf16, us, plain -> non-temporal): 16384^2 191 -> 178, 65536 x 4096 190 ->
+// 178, 32768^2 839 -> 809; at 256 MiB and below, where a part of the input may
+// still be cached, they lose (32768 x 4096 78.9 -> 85.5, 8192^2 40.4 -> 42.8), and
+// rows without 16-byte alignment gain nothing (131072 x 2049 189 -> 190).
+template <int DT>
+static bool launch_rows_t(const SoftmaxParams& p, bool aligned, hipStream_t s) {
+  const int64_t n = p.n;
+  const bool st = aligned && p.rows > ((int64_t)256 << 20) / 2 / n;
+  if (n <= 128) return launch_rows<DT, 16, 1>(p, st, s);
+  if (n <= 256) return launch_rows<DT, 16, 2>(p, st, s);
+  if (n <= 512) return launch_rows<DT, 64, 1>(p, st, s);
+  if (n <= 1024) return launch_rows<DT, 64, 2>(p, st, s);
+  if (n <= 2048) return launch_rows<DT, 64, 4>(p, st, s);
+  if (n <= 4096) return launch_rows<DT, 64, 8>(p, st, s);
+  if (n <= 8192) return launch_rows<DT, 256, 4>(p, st, s);
+  if (n <= 16384) return launch_rows<DT, 256, 8>(p, st, s);
+  if (n <= 32768) return launch_rows<DT, 1024, 4>(p, st, s);
+  if (n <= 65536) return launch_rows<DT, 1024, 8>(p, st, s);
+  if (n <= 131072) return launch_rows<DT, 1024, 16>(p, st, s);
+  return false;
+}
+
 hipError_t launch_softmax(const SoftmaxParams& p, int dtype, bool aligned, unsigned grid, hipStream_t s) {
   constexpr int W = kSoftmaxWaves, T = kSoftmaxTiles;
+  if (dtype == ATTN_BF16 ? launch_rows_t<ATTN_BF16>(p, aligned, s) : launch_rows_t<ATTN_F16>(p, aligned, s))
+    return hipGetLastError();
   if (dtype == ATTN_BF16) {
     if (aligned) hipLaunchKernelGGL((softmax_kernel<ATTN_BF16, W, T, true>), dim3(grid), dim3(W * 64), 0, s, p);
     else hipLaunchKernelGGL((softmax_kernel<ATTN_BF16, W, T, false>), dim3(grid), dim3(W * 64), 0, s, p);

@@ -100,3 +100,53 @@ def test_softmax_random_shapes(rows, n, dtype, spread):
     torch.cuda.synchronize()
     ref = SM.softmax_rows(inputs.bits_to_f64(x, dtype))
     _check(_gpu.download(ty, dtype), ref, dtype, f"random {rows}x{n}")
+
+
+# Row lengths on both sides of every boundary of the register-resident variants
+# (chunks of 8 per thread, threads per row), with row counts that leave the last
+# workgroup of the 16-lane and 64-lane variants partly empty.
+EDGE_N = [1, 7, 8, 9, 127, 128, 129, 256, 257, 511, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 16384,
+          16385, 32768, 32769, 65536, 65537, 131072, 131073]
+
+
+@pytest.mark.parametrize("n", EDGE_N)
+def test_softmax_row_length_edges(n):
+    """Each boundary length in both types, 16-byte aligned and one element off,
+    out of place and (f16) in place, with a row of -inf and a row of which only
+    one element is visible; elements around the output stay untouched."""
+    rows = 19 if n <= 1024 else 5
+    for dtype, off in (("bf16", 0), ("f16", 1)):
+        print(f"case softmax edge {rows}x{n} {dtype} offset {off}", flush=True)
+        xf = inputs.bits_to_f64(inputs.make_matrix(rows, n, dtype, seed=n + off, spread=2.0), dtype)
+        xf[1] = -np.inf
+        xf[2, :-1] = -np.inf
+        tx = torch.zeros(rows * n + 16, dtype=_gpu.torch_dtype(dtype), device="cuda")
+        x = tx[8 + off:8 + off + rows * n].view(rows, n)
+        x.copy_(torch.from_numpy(xf))
+        ty = torch.full_like(tx, 7.0)
+        y = ty[8 + off:8 + off + rows * n].view(rows, n)
+        capi.attn_softmax(x, y)
+        if off:
+            capi.attn_softmax(x, x)
+        torch.cuda.synchronize()
+        e = np.exp(xf - np.where(np.isinf(xf.max(1)), 0, xf.max(1))[:, None])
+        ref = e / np.maximum(e.sum(1), 1e-300)[:, None]
+        _check(_gpu.download(y, dtype), ref, dtype, f"{rows}x{n}")
+        assert (ty[:8 + off] == 7).all() and (ty[8 + off + rows * n:] == 7).all()
+        if off:
+            assert torch.equal(x.view(torch.int16), y.view(torch.int16))
+            assert (tx[:8 + off] == 0).all() and (tx[8 + off + rows * n:] == 0).all()
+
+
+@pytest.mark.parametrize("n,dtype", [(9, "bf16"), (100, "f16"), (257, "bf16"), (777, "f16"), (2049, "bf16"), (4100, "f16")])
+def test_softmax_causal_any_length(n, dtype):
+    """One square causal block of a length without 16-byte rows: every element,
+    zeros above the diagonal."""
+    print(f"case softmax causal {n} {dtype}", flush=True)
+    x = inputs.make_matrix(n, n, dtype, seed=n, spread=2.0)
+    ty = torch.full((n, n), float("nan"), dtype=_gpu.torch_dtype(dtype), device="cuda")
+    capi.attn_softmax(_gpu.upload(x, dtype), ty, causal=True)
+    torch.cuda.synchronize()
+    got = _gpu.download(ty, dtype)
+    _check(got, SM.softmax_rows(inputs.bits_to_f64(x, dtype), causal=True), dtype, f"causal {n}")
+    assert np.all(got[np.triu(np.ones((n, n), bool), 1)] == 0)
