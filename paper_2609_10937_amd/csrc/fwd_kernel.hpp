@@ -134,6 +134,7 @@ template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+  asm volatile("" ::: "memory");  // reads of what the copies wrote stay behind the wait
 }
 
 // One 16-byte-per-lane copy from global memory straight into LDS
@@ -582,20 +583,47 @@ __global__ void __launch_bounds__(NW * 64) fwd_kernel(const FwdParams p) {
 
   const float cs = p.c;  // scale * log2(e): scores in the base-2 domain
 
-  // Prologue copies: tile 0, then the Q loads, then tiles 1 .. AHEAD, so
-  // that the Q loads and the first tile travel together; both are complete
-  // once only the later tiles' copies are outstanding.
-  if (n > 0) issue(0, 0, NC);
-  // Q fragments: B operand of S^T = K Q^T, one 16-byte load per (block, k step).
+  // Prologue copies: tile 0, then the wave's Q rows, then tiles 1 .. AHEAD, so
+  // that Q and the first tile travel together; both are complete once only the
+  // later tiles' copies are outstanding.
+  // A Q fragment (B operand of S^T = K Q^T) is 16 rows x 64 bytes with adjacent
+  // lanes in different rows, a pattern the memory pipeline serves at 38 GB/s per
+  // CU where whole rows reach 175 (both from L2), so Q goes through LDS like a K
+  // tile (STAGED): the wave copies its own rows into the stages that no prologue
+  // tile uses and reads its fragments from there before the first barrier; and O
+  // leaves through LDS as whole rows (store_block).  With both, 8 heads at L =
+  // 1024 take 14.9 us instead of 17.8, one head at L = 4096 17.6 instead of 21.0, at
+  // L = 16384 112.6 instead of 115.5 (d = 128, with the merge).  Not for the padded
+  // rows of d = 96 (300 heads at L = 260 31.9 -> 32.7 us: three passes per wave) nor
+  // for one-wave workgroups, whose few rows do not fill the pipeline (8 heads at
+  // L = 300 13.4 -> 13.9 us): they keep the direct loads and stores.
+  constexpr bool STAGED = D == DL && NW > 1;
+  constexpr int QBLK = 16 * ROWB;  // LDS bytes of 16 Q rows
+  static_assert(!STAGED || QBLK % 1024 == 0 && NW * QB * QBLK <= (ST - 1 - AHEAD) * STAGEB, "Q staging");
+  const uint32_t qdst = (uint32_t)__builtin_amdgcn_readfirstlane(lds0 + (AHEAD + 1) * STAGEB + w * QB * QBLK);
   V8 qf[QB][KC];
+  if (n > 0) {
+    issue(0, 0, NC);
+    if constexpr (STAGED) {
+      const i32x4_t qrs =
+          buffer_rsrc(uniform_ptr(Qh) + (uint64_t)q0 * GROWB, (uint32_t)max(0, min(L - q0, TQW)) * GROWB);
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const int r = q0 + 16 * qb + c;
+      for (int i = 0; i < QB * QBLK / 1024; ++i) {
+        const int r = i * RPB + lane / KCH;
+        copy_to_lds_buf(qrs, (uint32_t)(r * GROWB + ((lane % KCH) ^ k_swz<KCH>(r)) * 16), qdst + i * 1024);
+      }
+    }
+  }
+  if constexpr (!STAGED) {
 #pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
-      u32x4_t x = {0u, 0u, 0u, 0u};
-      if (r < L) x = ldg16(Qh + (size_t)r * D + 32 * kc + 8 * g);
-      qf[qb][kc] = __builtin_bit_cast(V8, x);
+    for (int qb = 0; qb < QB; ++qb) {
+      const int r = q0 + 16 * qb + c;
+#pragma unroll
+      for (int kc = 0; kc < KC; ++kc) {
+        u32x4_t x = {0u, 0u, 0u, 0u};
+        if (r < L) x = ldg16(Qh + (size_t)r * D + 32 * kc + 8 * g);
+        qf[qb][kc] = __builtin_bit_cast(V8, x);
+      }
     }
   }
   if (n > 0) {
@@ -657,6 +685,14 @@ __global__ void __launch_bounds__(NW * 64) fwd_kernel(const FwdParams p) {
     ATTN_LDS const char* base = (ATTN_LDS const char*)(size_t)(kb0 ^ (uint32_t)(64 * kc));
     return __builtin_bit_cast(V8, *(ATTN_LDS const u32x4_t*)(base + kb * 16 * ROWB));
   };
+
+  if (STAGED && n > 0) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+      for (int kc = 0; kc < KC; ++kc) qf[qb][kc] = load_k(kbase + qdst, kc, qb);
+  }
 
   // The stage offsets pass through readfirstlane: as opaque wave-uniform
   // values they stay one scalar add per phase instead of becoming one
@@ -767,6 +803,33 @@ __global__ void __launch_bounds__(NW * 64) fwd_kernel(const FwdParams p) {
   auto store_row = [&](uint16_t* row, const f32x4_t (&acc)[NDB], float inv) ATTN_INLINE {
 #pragma unroll
     for (int db = 0; db < NDB; ++db) *reinterpret_cast<u32x2_t*>(row + 16 * db + 4 * g) = pack4(acc[db] * inv);
+  };
+  // STAGED: rows q0 + 16 qb .. + 15 of this wave, normalised, through a descriptor
+  // over the wave's rows of O or of the split's partials.  A fragment holds 8 bytes of each of 16 rows,
+  // and storing it as such moves 32 bytes of a row at a time (2.0 us for the
+  // workgroup's 64 KB); so the rows go through LDS, at most 256 bytes of each in
+  // a pass, and leave as whole rows.  The wave's 4 KB lie in the stage of tile
+  // n - 2 (n + 3 modulo the 5 stages): every wave had read that tile before the
+  // last barrier, and the copies of tiles past the range go to n .. n + 2.
+  auto store_block = [&](const __amdgpu_buffer_rsrc_t rs, int qb, float inv) ATTN_INLINE {
+    constexpr int PCH = KCH < 16 ? KCH : 16, PRB = PCH * 16;  // chunks and bytes of a row in a pass
+    static_assert(ST == 5 && AHEAD <= 2 && NW * 16 * PRB <= STAGEB, "store staging");
+    ATTN_LDS char* const buf =
+        lds + __builtin_amdgcn_readfirstlane(((max(n, 0) + 3) % ST) * STAGEB + w * 16 * PRB);
+#pragma unroll
+    for (int hp = 0; hp < KCH / PCH; ++hp) {
+#pragma unroll
+      for (int db = hp * PCH / 2; db < NDB && db < (hp + 1) * PCH / 2; ++db)
+        *(ATTN_LDS u32x2_t*)(buf + c * PRB + ((2 * db - hp * PCH + (g >> 1)) ^ k_swz<PCH>(c)) * 16 + 8 * (g & 1)) =
+            pack4(o[qb][db] * inv);
+#pragma unroll
+      for (int i = 0; i < 16 * PRB / 1024; ++i) {
+        // Rows past the sequence fall outside the descriptor and are dropped.
+        const int r = (64 * i + lane) / PCH, ch = lane % PCH;
+        const u32x4_t v = *(ATTN_LDS const u32x4_t*)(buf + r * PRB + (ch ^ k_swz<PCH>(r)) * 16);
+        __builtin_amdgcn_raw_buffer_store_b128(v, rs, (16 * qb + r) * GROWB + (hp * PCH + ch) * 16, 0, 0);
+      }
+    }
   };
   // PERSIST: the current unit's rows (no split), through a buffer descriptor
   // over its head's O, so rows past the sequence are dropped by the
@@ -956,24 +1019,27 @@ __global__ void __launch_bounds__(NW * 64) fwd_kernel(const FwdParams p) {
   if constexpr (PERSIST) {
     store_unit_rows();
   } else {
+    const size_t prow = ((size_t)split * p.BH + head) * (size_t)L + q0;  // row q0 of the split's partials
+    uint16_t* const dst = p.n_split == 1 ? static_cast<uint16_t*>(p.o) + hoff + (size_t)q0 * D
+                                         : static_cast<uint16_t*>(p.part_o) + prow * D;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(uniform_ptr(dst)), (short)0,
+                                          __builtin_amdgcn_readfirstlane(max(0, min(L - q0, TQW)) * GROWB), 0x00020000);
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
+      if (q0 + 16 * qb >= L) break;
       const float lt = lacc[qb][0];
       const float inv = lt > 0.f ? 1.f / lt : 0.f;
-      int q = q0 + 16 * qb + c;
+      int r = 16 * qb + c;
       // Row offsets at a d that is not a power of two are multiplications: keep
       // the compiler from carrying the Q loads' ones through the loop.
-      if constexpr (D != DL) asm volatile("" : "+v"(q));
-      if (q >= L) continue;
-      if (p.n_split == 1) {
-        store_row(static_cast<uint16_t*>(p.o) + hoff + (size_t)q * D, o[qb], inv);
-      } else {
-        const size_t prow = ((size_t)split * p.BH + head) * (size_t)L + q;
-        store_row(static_cast<uint16_t*>(p.part_o) + prow * D, o[qb], inv);
-        if (g == 0)
-          *reinterpret_cast<float2*>(p.part_ml + prow * 2) =
-              make_float2(lim[qb] == -INFINITY ? -INFINITY : mref[qb], lt);
-      }
+      if constexpr (D != DL) asm volatile("" : "+v"(r));
+      if constexpr (STAGED) store_block(rs, qb, inv);
+      if (q0 + r >= L) continue;
+      if constexpr (!STAGED) store_row(dst + (size_t)r * D, o[qb], inv);
+      if (p.n_split > 1 && g == 0)
+        *reinterpret_cast<float2*>(p.part_ml + (prow + r) * 2) =
+            make_float2(lim[qb] == -INFINITY ? -INFINITY : mref[qb], lt);
     }
   }
 }

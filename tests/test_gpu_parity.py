@@ -681,3 +681,23 @@ def test_random_shapes(B, H, L, d, causal, dtype, kx):
     o = _gpu.fused(_gpu.upload(q, dtype), _gpu.upload(k, dtype), _gpu.upload(v, dtype), scale, causal)
     ref = A.attention(_f64(q, dtype), _f64(k, dtype), _f64(v, dtype), scale, causal)
     _gpu.assert_close(_gpu.download(o, dtype), ref, dtype, f"random L{L} d{d}")
+
+
+@pytest.mark.parametrize("L", [1, 15, 17, 255, 257, 500, 2049])
+@pytest.mark.parametrize("d,dtype", [(64, "f16"), (96, "bf16"), (128, "bf16"), (256, "f16")])
+def test_rows_past_the_sequence_are_not_written(L, d, dtype):
+    """O leaves as whole rows through LDS: sequence lengths that end inside a
+    wave's 16-row block, with and without split key ranges, every row against the
+    oracle and the memory around O and around every head's rows untouched."""
+    for B, H, causal in ((1, 1, True), (1, 40, False)):
+        print(f"case row ends B{B} H{H} L{L} d{d} causal{int(causal)} {dtype}", flush=True)
+        q, k, v = inputs.make_qkv(B, H, L, d, dtype, seed=L * 3 + d)
+        s = inputs.softmax_scale(d)
+        n = B * H * L * d
+        buf = torch.full((n + 4096,), 3.0, dtype=_gpu.torch_dtype(dtype), device="cuda")
+        o = buf[2048:2048 + n].view(B, H, L, d)
+        capi.attn_fwd(_gpu.upload(q, dtype), _gpu.upload(k, dtype), _gpu.upload(v, dtype), o, s, causal)
+        torch.cuda.synchronize()
+        ref = A.attention(_f64(q, dtype), _f64(k, dtype), _f64(v, dtype), s, causal)
+        _gpu.assert_close(_gpu.download(o, dtype), ref, dtype, f"L{L} d{d}")
+        assert (buf[:2048] == 3).all() and (buf[2048 + n:] == 3).all()
