@@ -37,6 +37,8 @@ SOURCES = [
     "fwd_f16_d256.hip",
     "fwd_bf16_d96.hip",
     "fwd_f16_d96.hip",
+    "short_bf16.hip",
+    "short_f16.hip",
     "gemm_bf16.hip",
     "gemm_f16.hip",
     "gemm_f32.hip",

@@ -129,6 +129,7 @@ struct StreamWorkspace {
 struct FwdPlan {
   attn_tile_report_t rep;
   const FwdInstance* inst;
+  int short_rows;  // rows per workgroup of the short-sequence kernel, 0 when the plan does not take it
 };
 using PlanKey = std::tuple<int, int, int, int, int, int>;  // B, H, L, d, causal, dtype
 constexpr size_t kMaxPlans = 1024;
@@ -264,10 +265,48 @@ int plan(const attn_hw_desc_t* hw, int B, int H, int L, int d, int causal, int d
   return ATTN_OK;
 }
 
+// Rows per workgroup (16 or 32) of the short-sequence kernel for a plan with split
+// key ranges, or 0 when the fused kernel and the merge are expected to be as
+// fast.  Both sides are closed forms in microseconds with measured constants
+// (130 sampled split plans, BH 1 to 64, L 100 to 6000, every head dimension; the
+// rule picks within 2% of the faster side on average, and the picked plans run
+// 1.4 times as fast on average as the fused kernel and the merge do):
+//   fused   rounds of num_cus workgroups, each 8 us (prologue, stores, drain) and a
+//           step per key tile (1.6 us at d = 96 and 128; 1.9 at d = 64, whose tile
+//           has twice the scores; 1.2 at d = 256, whose tile has half the products),
+//           4 us for the merge launch, 2 for the masked tiles of causal pieces;
+//   short   4 us, and rounds of the workgroups that run at once (8 waves per
+//           CU, one per split up to 8, else one per two), each 1 us and 2.5 us per
+//           key tile of a wave (2.05 with 16 rows); over several rounds of causal row
+//           groups, heavy and light ones average to 0.75 of the heaviest.
+// E.g. 8 heads at L = 1024, d = 128: 15.1 us fused, 9.9 short; one head at L =
+// 8192 37 fused, 46 short (each workgroup streams all its keys from L2).
+int short_rows(const attn_tile_report_t& rep, int64_t heads, int L, int d, int causal, int num_cus) {
+  if (rep.n_split < 2 || rep.n_split > 16 || num_cus <= 0) return 0;
+  const double step = d == 64 ? 1.9 : d == 256 ? 1.2 : 1.6;
+  const double rounds_f = (double)((rep.grid + num_cus - 1) / num_cus);
+  const double fused = 4.0 + rounds_f * (8.0 + step * rep.tiles_per_split) + (causal ? 2.0 : 0.0);
+  const int per_wave = rep.n_split > 8 ? 2 : 1;
+  const int waves = (rep.n_split + per_wave - 1) / per_wave;
+  const int64_t slots = (int64_t)num_cus * (8 / waves);
+  int pick = 0;
+  double best = 0.95 * fused;
+  for (const int rows : {32, 16}) {
+    if (rows == 32 && (d == 256 || per_wave == 2)) continue;  // no such instance
+    const int64_t groups = heads * ((L + rows - 1) / rows);
+    const int64_t rounds = (groups + slots - 1) / slots;
+    const double tile = rows == 32 ? 2.5 : 2.05;
+    const double cost =
+        4.0 + rounds * (1.0 + tile * rep.tiles_per_split * per_wave) * (causal && rounds > 1 ? 0.75 : 1.0);
+    if (cost < best) best = cost, pick = rows;
+  }
+  return pick;
+}
+
 // The plan of a shape on the given device: derived on the device's first
 // call with that shape, then read from its table.
 int device_plan(int device, int B, int H, int L, int d, int causal, int dtype, attn_tile_report_t* rep,
-                const FwdInstance** inst) {
+                const FwdInstance** inst, int* rows) {
   std::lock_guard<std::mutex> lk(g_mu);
   DeviceState& st = g_dev[device];
   if (!st.have_desc) {
@@ -280,12 +319,14 @@ int device_plan(int device, int B, int H, int L, int d, int causal, int dtype, a
   if (it != st.plans.end()) {
     *rep = it->second.rep;
     *inst = it->second.inst;
+    *rows = it->second.short_rows;
     return ATTN_OK;
   }
   const int rc = plan(&st.desc, B, H, L, d, causal, dtype, rep, inst);
   if (rc != ATTN_OK) return rc;
   if (st.plans.size() >= kMaxPlans) st.plans.clear();
-  st.plans.emplace(key, FwdPlan{*rep, *inst});
+  *rows = short_rows(*rep, (int64_t)B * H, L, d, causal, st.desc.num_cus);
+  st.plans.emplace(key, FwdPlan{*rep, *inst, *rows});
   return ATTN_OK;
 }
 
@@ -303,7 +344,7 @@ int prepare(const void* Q, const void* K, const void* V, void* O, int B, int H, 
   if (rc != ATTN_OK) return rc;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return ATTN_E_HIP;
-  rc = device_plan(dev, B, H, L, d, causal, dtype, &out->rep, &out->inst);
+  rc = device_plan(dev, B, H, L, d, causal, dtype, &out->rep, &out->inst, &out->short_rows);
   if (rc != ATTN_OK) return rc;
   FwdParams& p = out->p;
   p = FwdParams{};
@@ -332,6 +373,13 @@ int prepare(const void* Q, const void* K, const void* V, void* O, int B, int H, 
 hipError_t launch_fused(const Prepared& pr, hipStream_t s) {
   const bool persist = pr.rep.launch_grid != pr.rep.grid;
   return (persist ? pr.inst->launch_persist : pr.inst->launch)(pr.p, (unsigned)pr.rep.launch_grid, s);
+}
+
+hipError_t launch_split(const Prepared& pr, int d, int dtype, hipStream_t s) {
+  if (pr.short_rows > 0)
+    return (dtype == ATTN_BF16 ? launch_short_bf16 : launch_short_f16)(pr.p, d, pr.short_rows, s);
+  const hipError_t e = launch_fused(pr, s);
+  return e == hipSuccess ? launch_combine(pr.p, d, dtype, s) : e;
 }
 
 void bind_workspace(FwdParams& p, void* ws, int d) {
@@ -489,8 +537,7 @@ int attn_fwd(const void* Q, const void* K, const void* V, void* O, int B, int H,
     w.bytes = grow;
   }
   bind_workspace(pr.p, w.ptr, d);
-  if (launch_fused(pr, s) != hipSuccess) return ATTN_E_HIP;
-  return launch_combine(pr.p, d, dtype, s) == hipSuccess ? ATTN_OK : ATTN_E_HIP;
+  return launch_split(pr, d, dtype, s) == hipSuccess ? ATTN_OK : ATTN_E_HIP;
 }
 
 int attn_fwd_workspace_bytes(int B, int H, int L, int d, int causal, int dtype, size_t* out) {

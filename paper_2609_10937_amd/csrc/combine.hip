@@ -7,15 +7,9 @@
 // w_s = l_s 2^(m_s - M), and the output is sum_s w_s (O_s / l_s) / sum_s w_s.
 // One thread per (row, 8 consecutive output columns): one 16-byte load per
 // split, one 16-byte store.
-#include "fwd_kernel.hpp"
+#include "merge.hpp"
 
 namespace attn {
-
-template <int DT>
-__device__ __forceinline__ float widen(uint16_t h) {
-  if constexpr (DT == ATTN_BF16) return __builtin_bit_cast(float, (uint32_t)h << 16);
-  else return (float)__builtin_bit_cast(_Float16, h);
-}
 
 // When the fused kernel ran every split of query tile t on XCD t % 8
 // (kOrderTiles), BY_TILE orders the merge's workgroups the same way: the
@@ -77,29 +71,7 @@ __global__ void __launch_bounds__(256) combine_kernel(const FwdParams p) {
   // Keep the scheduler from sinking loads below this point.
   __builtin_amdgcn_sched_barrier(0);
 
-  float m = -INFINITY;
-#pragma unroll
-  for (int s = 0; s < NS; ++s) m = fmaxf(m, st[s].x);
-  float lt = 0.f;
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    const float wgt = (s >= n_split || st[s].x == -INFINITY) ? 0.f : st[s].y * exp2_hw(st[s].x - m);
-    lt += wgt;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      acc[2 * e] += wgt * widen<DT>((uint16_t)(po[s][e] & 0xffffu));
-      acc[2 * e + 1] += wgt * widen<DT>((uint16_t)(po[s][e] >> 16));
-    }
-  }
-  const float inv = lt > 0.f ? 1.f / lt : 0.f;
-  uint32_t out[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const S a = (S)(acc[2 * e] * inv), b = (S)(acc[2 * e + 1] * inv);
-    out[e] = (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
-  }
-  *reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(p.o) + row * D + 8 * d8) = (u32x4_t){out[0], out[1], out[2], out[3]};
+  *reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(p.o) + row * D + 8 * d8) = merge_splits<DT, NS>(st, po, n_split);
 }
 
 template <int DT, int D, bool BY_TILE>

@@ -76,16 +76,26 @@ struct Prepared {
   const FwdInstance* inst;
   FwdParams p;
   size_t ws_bytes;  // split workspace the plan needs (0 without a split)
+  int short_rows;   // query rows per workgroup of the short-sequence kernel, 0 when the plan does not take it
 };
 int prepare(const void* Q, const void* K, const void* V, void* O, int B, int H, int L, int d, float scale, int causal,
             int dtype, Prepared* out);
 // Enqueue the fused kernel of a prepared call (persistent when the plan's
 // launch grid differs from its grid).
 hipError_t launch_fused(const Prepared& pr, hipStream_t s);
+// Enqueue a prepared call whose plan splits the key range: the short-sequence
+// kernel, or the fused kernel and the merge (the partials bound to a workspace).
+hipError_t launch_split(const Prepared& pr, int d, int dtype, hipStream_t s);
 // Point the split partials of `p` into a workspace of at least Prepared::ws_bytes.
 void bind_workspace(FwdParams& p, void* ws, int d);
 
 hipError_t launch_combine(const FwdParams& p, int d, int dtype, hipStream_t s);
+
+// The short-sequence kernel (short_kernel.hpp): a split plan's key ranges as the
+// waves of one workgroup of `rows` (16 or 32) query rows.
+constexpr int kShortRegion = 16384;  // LDS bytes of one wave: a V tile
+hipError_t launch_short_bf16(const FwdParams& p, int d, int rows, hipStream_t s);
+hipError_t launch_short_f16(const FwdParams& p, int d, int rows, hipStream_t s);
 
 // The unfused baseline's three steps: the row-softmax derivation for the
 // (B*H*L) x L score matrix and the GEMM derivations (and compiled instances)

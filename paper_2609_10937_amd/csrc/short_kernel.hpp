@@ -1,0 +1,385 @@
+// Fused attention forward for plans with split key ranges and short sequences:
+// the splits of a few query rows run side by side as the waves of one
+// workgroup and are merged through LDS, so the partial results never reach
+// device memory and there is no second launch.
+//
+// A workgroup takes R = 16 QB consecutive query rows of one head; wave w takes
+// split w (SPW = 2: splits w and w + 8) of the plan's key ranges, tile by tile
+// with the arithmetic of the fused kernel in the same order (the same
+// fragments, the same softmax step per 16-row block and key tile, the same
+// rounding of the normalised partials) and then the merge kernel's, so O is
+// bit for bit what the fused kernel and the merge kernel give.
+//
+// The waves share nothing until the merge, so there is no barrier in the loop.
+// Q, K and V reach a wave through 16 KB of LDS of its own as two 8 KB slots of
+// direct copies (whole rows: reading K fragments straight from memory, 16 rows x
+// 64 bytes with adjacent lanes in different rows, runs at 38 GB/s per CU instead
+// of 175): a tile is four pieces, K in two and V in two, and a piece is requested
+// as soon as the slot's previous piece has been read, two pieces ahead of its use.
+//
+// What bounds it is the K and V stream into the CU (each workgroup reads all
+// keys its rows see), where the fused kernel with 256 rows per workgroup pays
+// about 10 us per launch in filling its ring, writing the partials and draining,
+// and about 4 us for the merge launch; the rule of short_rows (capi.cpp) weighs
+// the two.
+#pragma once
+
+#include "merge.hpp"
+
+namespace attn {
+
+template <int DT, int D, int TKV, int QB, int SPW>
+__global__ void __launch_bounds__(512) short_kernel(const FwdParams p) {
+#ifdef __HIP_DEVICE_COMPILE__  // the body is device code only (LDS copies)
+  using M = Mfma<DT>;
+  using V8 = typename M::V8;
+  using S = typename M::S;
+  constexpr int R = 16 * QB;
+  constexpr int KC = D / 32, NKB = TKV / 16, NP = TKV / 32, NDB = D / 16;
+  constexpr int DL = (D & (D - 1)) == 0 ? D : (D <= 128 ? 128 : 256);  // elements of a row in LDS
+  constexpr int KCH = DL / 8;
+  constexpr int ROWB = DL * 2, GROWB = D * 2;
+  // A piece: PROWS rows of PCH 16-byte chunks.  d <= 128: half of the tile's rows;
+  // d = 256: half of the columns of all 32 rows.
+  constexpr int PCH = KCH < 16 ? KCH : 16, PROWB = PCH * 16, PIECE = 8192, PROWS = PIECE / PROWB;
+  constexpr bool HALF_COLS = KCH > PCH;
+  constexpr int NC = PIECE / 1024;  // copies of a piece
+  static_assert(TKV * ROWB == 2 * PIECE && 2 * PIECE == kShortRegion, "a K or V tile is two pieces");
+  static_assert(R * ROWB <= PIECE && SPW * R * ROWB <= 2 * PIECE, "Q fits a slot, the partials the region");
+  extern __shared__ __attribute__((aligned(1024))) unsigned char short_smem[];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nw = blockDim.x >> 6;
+  const int g = lane >> 4, c = lane & 15;
+  const int L = p.L;
+  // Workgroup -> (head, row group), so that the workgroups an XCD (block index mod
+  // 8) runs together share few heads' K and V through its L2.  BH up to 8 or a
+  // multiple of 8: heads fastest, then the row groups that see the most keys
+  // first (causal).  Else XCD x takes the x-th eighth of the workgroups in
+  // head-major order.
+  const int n_rg = (L + R - 1) / R, total = p.BH * n_rg;
+  int head, rank;
+  if (p.BH <= 8 || p.BH % 8 == 0) {
+    head = blockIdx.x % p.BH;
+    rank = blockIdx.x / p.BH;
+  } else {
+    const int t = (int)(blockIdx.x % 8) * ((total + 7) / 8) + (int)(blockIdx.x / 8);
+    head = t / n_rg;
+    rank = t - head * n_rg;
+  }
+  if (head >= p.BH || rank >= n_rg) return;  // the grid is a multiple of 8
+  const int rg = p.causal ? n_rg - 1 - rank : rank;
+  const int r0 = rg * R;
+  const size_t hoff = (size_t)head * (size_t)L * D;
+  const uint16_t* __restrict__ Qh = static_cast<const uint16_t*>(p.q) + hoff;
+  const uint64_t kh = uniform_ptr(static_cast<const uint16_t*>(p.k) + hoff);
+  const uint64_t vh = uniform_ptr(static_cast<const uint16_t*>(p.v) + hoff);
+
+  // Key tiles these rows see.
+  int nvis = (L + TKV - 1) / TKV;
+  if (p.causal) nvis = min(nvis, (min(L, r0 + R) + TKV - 1) / TKV);
+
+  ATTN_LDS char* const region = (ATTN_LDS char*)short_smem + w * kShortRegion;
+  const uint32_t reg0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(size_t)region);
+
+  // Copy offsets.  Copy i of a piece fills 16-byte slots 64 i + lane: row
+  // r = that / PCH, logical chunk (that % PCH) ^ swizzle(r); the pattern repeats
+  // every KP (VP) copies.  Rows past the sequence lie outside the tile's
+  // descriptor and arrive as zeros without touching memory (the mask removes
+  // their keys).
+  constexpr int RPC = 64 / PCH, KP = 16 / RPC, VP = 8 / RPC;
+  uint32_t koff[KP], voff[VP];
+  auto lane_off = [&](int i, bool is_v) ATTN_INLINE -> uint32_t {
+    const int r = i * RPC + lane / PCH;
+    int ch = (lane % PCH) ^ (is_v ? v_swz<PCH>(r) : k_swz<PCH>(r));
+    if constexpr (D != DL) ch = min(ch, D / 8 - 1);
+    return (uint32_t)(r * GROWB + ch * 16);
+  };
+#pragma unroll
+  for (int i = 0; i < KP; ++i) koff[i] = lane_off(i, false);
+#pragma unroll
+  for (int i = 0; i < VP; ++i) voff[i] = lane_off(i, true);
+  constexpr uint32_t HSTEP = HALF_COLS ? PROWB : PROWS * GROWB;  // from piece 0 to piece 1
+  // Piece h (0, 1) of K or V tile t into slot h.
+  auto copy_piece = [&](bool is_v, int t, int h) ATTN_INLINE {
+    const i32x4_t rs = buffer_rsrc((is_v ? vh : kh) + (uint64_t)t * (TKV * GROWB), (uint32_t)min(L - t * TKV, TKV) * GROWB);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      uint32_t o = is_v ? voff[i % VP] + (i / VP) * (VP * RPC * GROWB) : koff[i % KP] + (i / KP) * (KP * RPC * GROWB);
+      if (h) o += HSTEP;
+      copy_to_lds_buf(rs, o, reg0 + h * PIECE + i * 1024);
+    }
+  };
+  // Every read of a slot has returned before its next copies are requested.
+  auto reads_done = [&]() ATTN_INLINE {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto piece_ready = [&](bool one_behind) ATTN_INLINE {
+    __builtin_amdgcn_sched_barrier(0);
+    if (one_behind) wait_vmcnt<NC>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // Fragment addresses: a lane base XOR a per-fragment constant plus a row offset,
+  // as in the fused kernel.
+  const uint32_t kb0 = reg0 + (uint32_t)(c * PROWB + ((g ^ k_swz<PCH>(c)) & 3) * 16 + (k_swz<PCH>(c) >> 2) * 64);
+  auto load_k = [&](int h, int kc, int row) ATTN_INLINE -> V8 {
+    ATTN_LDS const char* base = (ATTN_LDS const char*)(size_t)(kb0 ^ (uint32_t)(64 * kc));
+    return __builtin_bit_cast(V8, *(ATTN_LDS const u32x4_t*)(base + h * PIECE + row * PROWB));
+  };
+  uint32_t vb0;
+  {
+    const int R0 = 4 * g + (c >> 2);
+    const int sw = v_swz<PCH>(R0);
+    vb0 = reg0 + (uint32_t)(R0 * PROWB + (((c & 3) >> 1) ^ (sw & 1)) * 16 + (sw >> 1) * 32 + 8 * (c & 1));
+  }
+  auto load_v = [&](int h, int row, int db) ATTN_INLINE -> V8 {
+    ATTN_LDS const char* base = (ATTN_LDS const char*)(size_t)(vb0 ^ (uint32_t)(32 * db));
+    const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ATTN_LDS i16x4_t*)(base + h * PIECE + row * PROWB));
+    const i16x4_t hi =
+        __builtin_amdgcn_ds_read_tr16_b64_v4i16((ATTN_LDS i16x4_t*)(base + h * PIECE + (row + 16) * PROWB));
+    const i16x8_t cat = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(V8, cat);
+  };
+  const float cs = p.c;
+
+  // Tiles of the wave's splits (causal: a split past the rows' last key has none,
+  // nor has any later one).
+  int t0s[SPW], ns[SPW];
+#pragma unroll
+  for (int sp = 0; sp < SPW; ++sp) {
+    const int split = w + sp * nw;
+    t0s[sp] = split * p.tiles_per_split;
+    ns[sp] = split < p.n_split ? max(0, min(nvis, t0s[sp] + p.tiles_per_split) - t0s[sp]) : 0;
+  }
+  // Q into slot 1, K piece 0 of the first tile into slot 0, then its K piece 1
+  // behind Q's reads.
+  V8 qf[QB][KC];
+  if (ns[0] > 0) {
+    constexpr int QCP = R * ROWB / 1024, RPQ = 64 / KCH;
+    const i32x4_t rs = buffer_rsrc(uniform_ptr(Qh + (size_t)r0 * D), (uint32_t)min(L - r0, R) * GROWB);
+#pragma unroll
+    for (int i = 0; i < QCP; ++i) {
+      const int r = i * RPQ + lane / KCH;
+      int ch = (lane % KCH) ^ k_swz<KCH>(r);
+      if constexpr (D != DL) ch = min(ch, D / 8 - 1);
+      copy_to_lds_buf(rs, (uint32_t)(r * GROWB + ch * 16), reg0 + PIECE + i * 1024);
+    }
+    copy_piece(false, t0s[0], 0);
+    piece_ready(true);
+    const uint32_t qb0 =
+        reg0 + PIECE + (uint32_t)(c * ROWB + ((g ^ k_swz<KCH>(c)) & 3) * 16 + (k_swz<KCH>(c) >> 2) * 64);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+      for (int kc = 0; kc < KC; ++kc)
+        qf[qb][kc] = __builtin_bit_cast(
+            V8, *(ATTN_LDS const u32x4_t*)((ATTN_LDS const char*)(size_t)(qb0 ^ (uint32_t)(64 * kc)) + qb * 16 * ROWB));
+    reads_done();
+    copy_piece(false, t0s[0], 1);
+  }
+
+  // One split after the other; its normalised partial stays packed in registers
+  // until the wave has read its last piece.
+  u32x2_t part[SPW][QB][NDB];
+  float pm[SPW][QB], pl[SPW][QB];
+#pragma unroll
+  for (int sp = 0; sp < SPW; ++sp) {
+    const int t0 = t0s[sp], n = ns[sp];
+    f32x4_t o[QB][NDB], lacc[QB];
+    float mref[QB], lim[QB], corr[QB];
+    bool rescale = false;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      mref[qb] = 0.f;
+      lim[qb] = -INFINITY;
+      corr[qb] = 1.f;
+      lacc[qb] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) o[qb][db] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    }
+#pragma clang loop unroll(disable)
+    for (int j = 0; j < n; ++j) {
+      const int t = t0 + j;
+      int tn = j + 1 < n ? t + 1 : -1;  // the tile after this one, -1 if none
+      if (sp + 1 < SPW && tn < 0 && ns[SPW - 1] > 0) tn = t0s[SPW - 1];
+      f32x4_t s[NKB][QB];
+      V8 pk[NP][QB];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        piece_ready(true);
+        constexpr int KB = HALF_COLS ? NKB : NKB / 2, KH = HALF_COLS ? KC / 2 : KC;
+        // The piece's fragments, read ahead of their products.
+        V8 kf[KH][KB];
+#pragma unroll
+        for (int kcl = 0; kcl < KH; ++kcl)
+#pragma unroll
+          for (int kbl = 0; kbl < KB; ++kbl) kf[kcl][kbl] = load_k(h, kcl, 16 * kbl);
+#pragma unroll
+        for (int kcl = 0; kcl < KH; ++kcl)
+#pragma unroll
+          for (int kbl = 0; kbl < KB; ++kbl) {
+            const int kb = HALF_COLS ? kbl : h * KB + kbl, kc = HALF_COLS ? h * KH + kcl : kcl;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb)
+              s[kb][qb] =
+                  M::run(kf[kcl][kbl], qf[qb][kc], kc == 0 ? (f32x4_t){0.f, 0.f, 0.f, 0.f} : s[kb][qb]);
+          }
+        __builtin_amdgcn_sched_group_barrier(0x100, KH * KB, 0);       // DS reads
+        __builtin_amdgcn_sched_group_barrier(0x008, KH * KB * QB, 0);  // matrix products
+        reads_done();
+        copy_piece(true, t, h);
+      }
+      const int kv0 = t * TKV;
+      if ((kv0 + TKV > L) || (p.causal && kv0 + TKV - 1 > r0))
+        softmax_tile<true, M>(s, pk, mref, lim, corr, rescale, kv0, r0, g, c, L, p.causal, cs);
+      else
+        softmax_tile<false, M>(s, pk, mref, lim, corr, rescale, kv0, r0, g, c, L, p.causal, cs);
+      if (rescale) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+#pragma unroll
+          for (int db = 0; db < NDB; ++db) o[qb][db] *= corr[qb];
+          lacc[qb] *= corr[qb];
+          corr[qb] = 1.f;
+        }
+        rescale = false;
+      }
+      const V8 ones = __builtin_bit_cast(V8, (u32x4_t){kOne2<DT>, kOne2<DT>, kOne2<DT>, kOne2<DT>});
+#pragma unroll
+      for (int pp = 0; pp < NP; ++pp)
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) lacc[qb] = M::run(ones, pk[pp][qb], lacc[qb]);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        piece_ready(h == 0 || tn >= 0);
+        constexpr int PP = HALF_COLS ? NP : NP / 2, DB = HALF_COLS ? NDB / 2 : NDB;
+        V8 vf[PP][DB];
+#pragma unroll
+        for (int ppl = 0; ppl < PP; ++ppl)
+#pragma unroll
+          for (int dbl = 0; dbl < DB; ++dbl) vf[ppl][dbl] = load_v(h, 32 * ppl, dbl);
+#pragma unroll
+        for (int ppl = 0; ppl < PP; ++ppl)
+#pragma unroll
+          for (int dbl = 0; dbl < DB; ++dbl) {
+            const int pp = HALF_COLS ? ppl : h * PP + ppl, db = HALF_COLS ? h * DB + dbl : dbl;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) o[qb][db] = M::run(vf[ppl][dbl], pk[pp][qb], o[qb][db]);
+          }
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 * PP * DB, 0);   // DS reads
+        __builtin_amdgcn_sched_group_barrier(0x008, PP * DB * QB, 0);  // matrix products
+        reads_done();
+        if (tn >= 0) copy_piece(false, tn, h);
+      }
+    }
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const float lt = lacc[qb][0];
+      const float inv = lt > 0.f ? 1.f / lt : 0.f;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) {
+        const f32x4_t v = o[qb][db] * inv;
+        S h4[4] = {(S)v[0], (S)v[1], (S)v[2], (S)v[3]};
+        part[sp][qb][db] = (u32x2_t){(uint32_t)__builtin_bit_cast(uint16_t, h4[0]) |
+                                         ((uint32_t)__builtin_bit_cast(uint16_t, h4[1]) << 16),
+                                     (uint32_t)__builtin_bit_cast(uint16_t, h4[2]) |
+                                         ((uint32_t)__builtin_bit_cast(uint16_t, h4[3]) << 16)};
+      }
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) asm volatile("" : "+v"(part[sp][qb][db]));
+      pm[sp][qb] = lim[qb] == -INFINITY ? -INFINITY : mref[qb];
+      pl[sp][qb] = lt;
+    }
+  }
+
+  // Partials to LDS: split s in region s % nw, slot s / nw, rows of DL elements
+  // in 16-byte chunks, XOR-swizzled so that a fragment store spreads over the
+  // banks; references and sums behind the regions, [split][row].
+  ATTN_LDS float2* const ml = (ATTN_LDS float2*)((ATTN_LDS char*)short_smem + nw * kShortRegion);
+#pragma unroll
+  for (int sp = 0; sp < SPW; ++sp)
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const int r = 16 * qb + c;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) {
+        const int ch = (2 * db + (g >> 1)) ^ k_swz<KCH>(r);
+        *(ATTN_LDS u32x2_t*)(region + sp * R * ROWB + r * ROWB + ch * 16 + 8 * (g & 1)) = part[sp][qb][db];
+      }
+      if (g == 0) {
+        ATTN_LDS float2* const e = ml + (w + sp * nw) * R + r;
+        e->x = pm[sp][qb];
+        e->y = pl[sp][qb];
+      }
+    }
+  __syncthreads();
+
+  // Merge: one (row, octet) item per thread and turn.
+  constexpr int OCTS = D / 8;
+  auto merge = [&](auto nsc) ATTN_INLINE {
+    constexpr int NS = decltype(nsc)::value;
+    for (int it = tid; it < R * OCTS; it += blockDim.x) {
+      const int r = it / OCTS, d8 = it - r * OCTS, q = r0 + r;
+      if (q >= L) continue;
+      int n = p.n_split;
+      if (p.pieces > 0) {
+        // Causal pieces: the row's query tile has one piece per tiles_per_split
+        // of the key tiles it sees.
+        const int qt = q / p.tile_q;
+        const int seen = (min(L, (qt + 1) * p.tile_q) + TKV - 1) / TKV;
+        n = (seen + p.tiles_per_split - 1) / p.tiles_per_split;
+      }
+      float2 st[NS];
+      u32x4_t po[NS];
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int sc = min(s, n - 1);
+        const int slot = SPW == 1 ? 0 : sc / nw, reg = SPW == 1 ? sc : sc % nw;
+        st[s].x = ml[sc * R + r].x;
+        st[s].y = ml[sc * R + r].y;
+        po[s] = *(ATTN_LDS const u32x4_t*)((ATTN_LDS char*)short_smem + reg * kShortRegion + slot * R * ROWB + r * ROWB +
+                                           (d8 ^ k_swz<KCH>(r)) * 16);
+      }
+      *reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(p.o) + hoff + (size_t)q * D + 8 * d8) =
+          merge_splits<DT, NS>(st, po, n);
+    }
+  };
+  if constexpr (SPW == 2) merge(std::integral_constant<int, 16>{});
+  else if (p.n_split <= 2) merge(std::integral_constant<int, 2>{});
+  else if (p.n_split <= 4) merge(std::integral_constant<int, 4>{});
+  else merge(std::integral_constant<int, 8>{});
+#endif
+}
+
+template <int DT, int D, int TKV, int QB, int SPW>
+hipError_t launch_short_i(const FwdParams& p, hipStream_t s) {
+  const int nw = (p.n_split + SPW - 1) / SPW;
+  const unsigned lds = nw * kShortRegion + p.n_split * 16 * QB * (unsigned)sizeof(float2) + (SPW == 2 ? 128 : 0);
+  const int64_t grid = ((int64_t)p.BH * ((p.L + 16 * QB - 1) / (16 * QB)) + 7) / 8 * 8;
+  if (p.n_split < 1 || nw > 8 || grid > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((short_kernel<DT, D, TKV, QB, SPW>), dim3((unsigned)grid), dim3(64 * nw), lds, s, p);
+  return hipGetLastError();
+}
+
+template <int DT>
+hipError_t launch_short_t(const FwdParams& p, int d, int rows, hipStream_t s) {
+  const bool two = p.n_split > 8;
+  if (d == 256) return two ? launch_short_i<DT, 256, 32, 1, 2>(p, s) : launch_short_i<DT, 256, 32, 1, 1>(p, s);
+  if (d == 128) {
+    if (two) return launch_short_i<DT, 128, 64, 1, 2>(p, s);
+    return rows == 32 ? launch_short_i<DT, 128, 64, 2, 1>(p, s) : launch_short_i<DT, 128, 64, 1, 1>(p, s);
+  }
+  if (d == 96) {
+    if (two) return launch_short_i<DT, 96, 64, 1, 2>(p, s);
+    return rows == 32 ? launch_short_i<DT, 96, 64, 2, 1>(p, s) : launch_short_i<DT, 96, 64, 1, 1>(p, s);
+  }
+  if (two) return launch_short_i<DT, 64, 128, 1, 2>(p, s);
+  return rows == 32 ? launch_short_i<DT, 64, 128, 2, 1>(p, s) : launch_short_i<DT, 64, 128, 1, 1>(p, s);
+}
+
+}  // namespace attn

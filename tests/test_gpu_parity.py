@@ -701,3 +701,71 @@ def test_rows_past_the_sequence_are_not_written(L, d, dtype):
         ref = A.attention(_f64(q, dtype), _f64(k, dtype), _f64(v, dtype), s, causal)
         _gpu.assert_close(_gpu.download(o, dtype), ref, dtype, f"L{L} d{d}")
         assert (buf[:2048] == 3).all() and (buf[2048 + n:] == 3).all()
+
+
+def _short_rows(r, BH, L, d, causal):
+    """The short-sequence kernel's rule restated: rows per workgroup, or 0."""
+    if not 2 <= r.n_split <= 16:
+        return 0
+    step = {64: 1.9, 256: 1.2}.get(d, 1.6)
+    best = 0.95 * (4 + -(-r.grid // 256) * (8 + step * r.tiles_per_split) + (2 if causal else 0))
+    per_wave = 2 if r.n_split > 8 else 1
+    waves = -(-r.n_split // per_wave)
+    pick = 0
+    for rows, tile in ((32, 2.5), (16, 2.05)):
+        if rows == 32 and (d == 256 or per_wave == 2):
+            continue
+        rounds = -(-(BH * -(-L // rows)) // (256 * (8 // waves)))
+        cost = 4 + rounds * (1 + tile * r.tiles_per_split * per_wave) * (0.75 if causal and rounds > 1 else 1)
+        if cost < best:
+            best, pick = cost, rows
+    return pick
+
+
+# (B, H, L, d, causal, type): every instance of the short-sequence kernel (rows per
+# workgroup, splits per wave), ragged ends, causal pieces, heads past 8 that 8 does
+# not divide, two rounds of workgroups
+SHORT = [
+    (1, 8, 1024, 128, False, "bf16"), (1, 8, 1024, 128, True, "f16"), (1, 16, 1000, 128, True, "bf16"),
+    (1, 8, 300, 128, False, "f16"), (1, 1, 697, 128, False, "bf16"), (3, 15, 129, 128, True, "bf16"),
+    (1, 8, 1024, 64, False, "f16"), (1, 9, 257, 64, True, "bf16"), (1, 2, 1561, 64, True, "f16"), (1, 61, 511, 64, False, "bf16"),
+    (1, 4, 1000, 96, False, "bf16"), (2, 5, 515, 96, True, "f16"), (1, 7, 112, 96, False, "f16"), (1, 60, 399, 96, False, "bf16"),
+    (1, 4, 1024, 256, False, "bf16"), (1, 9, 110, 256, True, "f16"), (1, 3, 500, 256, True, "bf16"), (1, 13, 65, 256, False, "f16"),
+]
+
+
+def test_short_sequence_cases_reach_every_instance():
+    got = set()
+    for B, H, L, d, causal, dtype in SHORT:
+        r = capi.attn_fwd_plan(B, H, L, d, causal, capi.ATTN_BF16 if dtype == "bf16" else capi.ATTN_F16)
+        rows = _short_rows(r, B * H, L, d, causal)
+        assert rows, (B, H, L, d)
+        got.add((d, rows, 2 if r.n_split > 8 else 1))
+    assert got >= {(d, r, s) for d in (64, 96, 128) for r, s in ((32, 1), (16, 1), (16, 2))} | {(256, 16, 1), (256, 16, 2)}
+
+
+@pytest.mark.parametrize("B,H,L,d,causal,dtype", SHORT)
+def test_short_sequence_kernel_equals_partial_and_merge(B, H, L, d, causal, dtype):
+    """attn_fwd (and attn_fwd_noalloc) on plans that take the short-sequence
+    kernel: bit for bit attn_fwd_partial + attn_fwd_merge, every row within the
+    bar of the oracle, nothing written around O."""
+    print(f"case short B{B} H{H} L{L} d{d} causal{int(causal)} {dtype}", flush=True)
+    dt = capi.ATTN_BF16 if dtype == "bf16" else capi.ATTN_F16
+    q, k, v = inputs.make_qkv(B, H, L, d, dtype, seed=L * 5 + d, k_scale=3.0)
+    tq, tk, tv = (_gpu.upload(x, dtype) for x in (q, k, v))
+    s = inputs.softmax_scale(d)
+    n = B * H * L * d
+    buf = torch.full((n + 4096,), 3.0, dtype=tq.dtype, device="cuda")
+    o = buf[2048:2048 + n].view(B, H, L, d)
+    capi.attn_fwd(tq, tk, tv, o, s, causal)
+    ws = torch.empty(capi.attn_fwd_workspace_bytes(B, H, L, d, causal, dt), dtype=torch.uint8, device="cuda")
+    two, na = torch.empty_like(tq), torch.empty_like(tq)
+    capi.attn_fwd_partial(tq, tk, tv, two, s, causal, ws)
+    capi.attn_fwd_merge(ws, two, s, causal)
+    capi.attn_fwd_noalloc(tq, tk, tv, na, s, causal)
+    torch.cuda.synchronize()
+    assert torch.equal(o.view(torch.int16), two.view(torch.int16))
+    assert torch.equal(o.view(torch.int16), na.view(torch.int16))
+    assert (buf[:2048] == 3).all() and (buf[2048 + n:] == 3).all()
+    ref = A.attention(_f64(q, dtype), _f64(k, dtype), _f64(v, dtype), s, causal)
+    _gpu.assert_close(_gpu.download(o, dtype), ref, dtype, f"short L{L} d{d}")
