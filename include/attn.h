@@ -184,9 +184,10 @@ int attn_fwd_plan(const attn_hw_desc_t* hw, int B, int H, int L, int d, int caus
  * workgroup per CU, each taking its share of the query tiles back to back
  * (the result is the same, bit for bit).  The plan of each shape is derived
  * once per device and kept (at most 1024 shapes, then the table starts over).
- * Split plans of short sequences run as one launch instead of two, the splits
- * of 16 or 32 query rows side by side in one workgroup and merged there (the
- * result is the same, bit for bit).
+ * Short sequences run as one launch of smaller workgroups instead, 16 or 32
+ * query rows each, the splits of these rows side by side as its waves and merged
+ * there (the result is the same, bit for bit; attn_fwd_partial always follows the
+ * plan's report).
  * Ownership and ordering: the call only enqueues work on `stream`; it never
  * synchronises.  The merge's workspace belongs to the library: one buffer per
  * (device, stream), so concurrent calls on different streams never share

@@ -265,31 +265,72 @@ int plan(const attn_hw_desc_t* hw, int B, int H, int L, int d, int causal, int d
   return ATTN_OK;
 }
 
-// Rows per workgroup (16 or 32) of the short-sequence kernel for a plan with split
-// key ranges, or 0 when the fused kernel and the merge are expected to be as
-// fast.  Both sides are closed forms in microseconds with measured constants
-// (130 sampled split plans, BH 1 to 64, L 100 to 6000, every head dimension; the
-// rule picks within 2% of the faster side on average, and the picked plans run
-// 1.4 times as fast on average as the fused kernel and the merge do):
+// Key tiles that all blocks of `rows` query rows of one head see together, and
+// the most that one of them sees.
+struct SeenTiles {
+  int64_t blocks, total, most;
+};
+SeenTiles seen_tiles(int L, int rows, int t_kv, int causal) {
+  const int64_t n_kv = (L + t_kv - 1) / t_kv, blocks = (L + rows - 1) / rows;
+  if (!causal) return {blocks, blocks * n_kv, n_kv};
+  int64_t total = 0;
+  for (int64_t i = 0; i < blocks; ++i)
+    total += std::min(n_kv, (std::min<int64_t>(L, (i + 1) * rows) + t_kv - 1) / t_kv);
+  return {blocks, total, n_kv};
+}
+
+// Rows per workgroup (16 or 32) of the short-sequence kernel for a plan, or 0
+// where the fused kernel (and the merge) are expected to be as fast.  Both sides
+// are closed forms in microseconds with measured constants.  A step is the fused
+// kernel's time per key tile: 1.6 us at d = 96 and 128, 1.9 at d = 64 (twice the
+// scores per tile), and at d = 256 (half the products) 1.0 to 1.2.
+//
+// Split key ranges (130 sampled plans, BH 1 to 64, L 100 to 6000, every d: the
+// picks run 1.40 times as fast as the two launches on average, the best choice
+// 1.42 times):
 //   fused   rounds of num_cus workgroups, each 8 us (prologue, stores, drain) and a
-//           step per key tile (1.6 us at d = 96 and 128; 1.9 at d = 64, whose tile
-//           has twice the scores; 1.2 at d = 256, whose tile has half the products),
-//           4 us for the merge launch, 2 for the masked tiles of causal pieces;
+//           step per key tile, 4 us for the merge launch, 2 for the masked tiles
+//           of causal pieces;
 //   short   4 us, and rounds of the workgroups that run at once (8 waves per
 //           CU, one per split up to 8, else one per two), each 1 us and 2.5 us per
 //           key tile of a wave (2.05 with 16 rows); over several rounds of causal row
 //           groups, heavy and light ones average to 0.75 of the heaviest.
 // E.g. 8 heads at L = 1024, d = 128: 15.1 us fused, 9.9 short; one head at L =
 // 8192 37 fused, 46 short (each workgroup streams all its keys from L2).
+//
+// No split (110 sampled plans, BH 1 to 512, L 64 to 2500: 1.13 times as fast on
+// average, the best choice 1.14 times), where a query tile of 256 rows costs more
+// in its fixed part than in its few key tiles, or is partly past the sequence:
+//   fused   2 us, and rounds of num_cus workgroups of 7 us and a step per key tile;
+//   short   4 us, and per CU 0.6 us per one-wave workgroup and 0.35 per key tile
+//           of a wave (16 rows: 0.3, and 0.26, at d = 256 0.35), but at least 4.6 us and
+//           1.5 (1.0) per key tile of the longest wave.
+// E.g. 300 heads at L = 100, d = 128: 15.2 us fused, 9.2 short; 1000 heads 35 and
+// 23; 300 heads at L = 700 102 and 105.  One-wave fused workgroups of at most one
+// round are as short already.
 int short_rows(const attn_tile_report_t& rep, int64_t heads, int L, int d, int causal, int num_cus) {
-  if (rep.n_split < 2 || rep.n_split > 16 || num_cus <= 0) return 0;
-  const double step = d == 64 ? 1.9 : d == 256 ? 1.2 : 1.6;
+  if (rep.n_split < 1 || rep.n_split > 16 || num_cus <= 0) return 0;
+  const double step = d == 64 ? 1.9 : d == 256 ? (rep.n_split == 1 ? 1.0 : 1.2) : 1.6;
   const double rounds_f = (double)((rep.grid + num_cus - 1) / num_cus);
+  int pick = 0;
+  if (rep.n_split == 1) {
+    if ((rep.n_waves == 1 && rep.grid <= num_cus) || (L + rep.t_kv - 1) / rep.t_kv > 32) return 0;
+    const SeenTiles q = seen_tiles(L, rep.tile_q, rep.t_kv, causal);
+    double best = (d == 256 ? 0.8 : 0.95) * (2.0 + rounds_f * (7.0 + step * q.total / q.blocks));
+    for (const int rows : {32, 16}) {
+      if (rows == 32 && d == 256) continue;  // no such instance
+      const SeenTiles w = seen_tiles(L, rows, rep.t_kv, causal);
+      const double wg = rows == 32 ? 0.6 : 0.3, tile = rows == 16 && d != 256 ? 0.26 : 0.35;
+      const double cost = std::max(4.0 + heads * (w.blocks * wg + w.total * tile) / num_cus,
+                                   4.6 + (rows == 32 ? 1.5 : 1.0) * w.most);
+      if (cost < best) best = cost, pick = rows;
+    }
+    return pick;
+  }
   const double fused = 4.0 + rounds_f * (8.0 + step * rep.tiles_per_split) + (causal ? 2.0 : 0.0);
   const int per_wave = rep.n_split > 8 ? 2 : 1;
   const int waves = (rep.n_split + per_wave - 1) / per_wave;
   const int64_t slots = (int64_t)num_cus * (8 / waves);
-  int pick = 0;
   double best = 0.95 * fused;
   for (const int rows : {32, 16}) {
     if (rows == 32 && (d == 256 || per_wave == 2)) continue;  // no such instance
@@ -375,11 +416,11 @@ hipError_t launch_fused(const Prepared& pr, hipStream_t s) {
   return (persist ? pr.inst->launch_persist : pr.inst->launch)(pr.p, (unsigned)pr.rep.launch_grid, s);
 }
 
-hipError_t launch_split(const Prepared& pr, int d, int dtype, hipStream_t s) {
+hipError_t launch_forward(const Prepared& pr, int d, int dtype, hipStream_t s) {
   if (pr.short_rows > 0)
     return (dtype == ATTN_BF16 ? launch_short_bf16 : launch_short_f16)(pr.p, d, pr.short_rows, s);
   const hipError_t e = launch_fused(pr, s);
-  return e == hipSuccess ? launch_combine(pr.p, d, dtype, s) : e;
+  return e == hipSuccess && pr.p.n_split > 1 ? launch_combine(pr.p, d, dtype, s) : e;
 }
 
 void bind_workspace(FwdParams& p, void* ws, int d) {
@@ -516,7 +557,7 @@ int attn_fwd(const void* Q, const void* K, const void* V, void* O, int B, int H,
   int rc = prepare(Q, K, V, O, B, H, L, d, scale, causal, dtype, &pr);
   if (rc != ATTN_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (pr.ws_bytes == 0) return launch_fused(pr, s) == hipSuccess ? ATTN_OK : ATTN_E_HIP;
+  if (pr.ws_bytes == 0) return launch_forward(pr, d, dtype, s) == hipSuccess ? ATTN_OK : ATTN_E_HIP;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return ATTN_E_HIP;
   // The lock covers binding the stream's buffer and enqueueing both kernels,
@@ -537,7 +578,7 @@ int attn_fwd(const void* Q, const void* K, const void* V, void* O, int B, int H,
     w.bytes = grow;
   }
   bind_workspace(pr.p, w.ptr, d);
-  return launch_split(pr, d, dtype, s) == hipSuccess ? ATTN_OK : ATTN_E_HIP;
+  return launch_forward(pr, d, dtype, s) == hipSuccess ? ATTN_OK : ATTN_E_HIP;
 }
 
 int attn_fwd_workspace_bytes(int B, int H, int L, int d, int causal, int dtype, size_t* out) {

@@ -83,16 +83,16 @@ int prepare(const void* Q, const void* K, const void* V, void* O, int B, int H, 
 // Enqueue the fused kernel of a prepared call (persistent when the plan's
 // launch grid differs from its grid).
 hipError_t launch_fused(const Prepared& pr, hipStream_t s);
-// Enqueue a prepared call whose plan splits the key range: the short-sequence
-// kernel, or the fused kernel and the merge (the partials bound to a workspace).
-hipError_t launch_split(const Prepared& pr, int d, int dtype, hipStream_t s);
+// Enqueue a prepared call whole: the short-sequence kernel, or the fused kernel
+// and, for split key ranges, the merge (the partials bound to a workspace).
+hipError_t launch_forward(const Prepared& pr, int d, int dtype, hipStream_t s);
 // Point the split partials of `p` into a workspace of at least Prepared::ws_bytes.
 void bind_workspace(FwdParams& p, void* ws, int d);
 
 hipError_t launch_combine(const FwdParams& p, int d, int dtype, hipStream_t s);
 
-// The short-sequence kernel (short_kernel.hpp): a split plan's key ranges as the
-// waves of one workgroup of `rows` (16 or 32) query rows.
+// The short-sequence kernel (short_kernel.hpp): a plan's key ranges (one or
+// several) as the waves of one workgroup of `rows` (16 or 32) query rows.
 constexpr int kShortRegion = 16384;  // LDS bytes of one wave: a V tile
 hipError_t launch_short_bf16(const FwdParams& p, int d, int rows, hipStream_t s);
 hipError_t launch_short_f16(const FwdParams& p, int d, int rows, hipStream_t s);

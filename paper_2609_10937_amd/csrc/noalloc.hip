@@ -55,6 +55,5 @@ extern "C" int attn_fwd_noalloc(const void* Q, const void* K, const void* V, voi
     if (rc != ATTN_OK) return rc;
     bind_workspace(pr.p, ws, d);
   }
-  const hipError_t e = pr.ws_bytes > 0 ? launch_split(pr, d, dtype, s) : launch_fused(pr, s);
-  return e == hipSuccess ? ATTN_OK : ATTN_E_HIP;
+  return launch_forward(pr, d, dtype, s) == hipSuccess ? ATTN_OK : ATTN_E_HIP;
 }

@@ -1,7 +1,9 @@
-// Fused attention forward for plans with split key ranges and short sequences:
-// the splits of a few query rows run side by side as the waves of one
-// workgroup and are merged through LDS, so the partial results never reach
-// device memory and there is no second launch.
+// Fused attention forward for short sequences: the splits (one or several) of a
+// few query rows run side by side as the waves of one workgroup and are merged
+// through LDS, so the partial results never reach device memory and there is no
+// second launch; without a split a workgroup is one wave, which leaves no
+// lane on rows past a short sequence and overlaps the fixed parts of many
+// workgroups on a CU.
 //
 // A workgroup takes R = 16 QB consecutive query rows of one head; wave w takes
 // split w (SPW = 2: splits w and w + 8) of the plan's key ranges, tile by tile
@@ -28,13 +30,19 @@
 
 namespace attn {
 
-template <int DT, int D, int TKV, int QB, int SPW>
+// Whether the grid spells out (head mod 8, row group, head / 8); otherwise it is
+// one dimension, the workgroups rounded up to a multiple of 8.
+__host__ __device__ inline bool short_grid_by_head(int BH) { return BH < 8 || (BH % 8 == 0 && BH / 8 <= 65535); }
+
+// SPLITS = 0: a plan without a split, one wave per workgroup, which writes O
+// itself; 1 or 2: splits per wave.
+template <int DT, int D, int TKV, int QB, int SPLITS>
 __global__ void __launch_bounds__(512) short_kernel(const FwdParams p) {
 #ifdef __HIP_DEVICE_COMPILE__  // the body is device code only (LDS copies)
   using M = Mfma<DT>;
   using V8 = typename M::V8;
   using S = typename M::S;
-  constexpr int R = 16 * QB;
+  constexpr int R = 16 * QB, SPW = SPLITS == 2 ? 2 : 1;
   constexpr int KC = D / 32, NKB = TKV / 16, NP = TKV / 32, NDB = D / 16;
   constexpr int DL = (D & (D - 1)) == 0 ? D : (D <= 128 ? 128 : 256);  // elements of a row in LDS
   constexpr int KCH = DL / 8;
@@ -49,26 +57,29 @@ __global__ void __launch_bounds__(512) short_kernel(const FwdParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char short_smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nw = blockDim.x >> 6;
+  const int w = SPLITS == 0 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nw = SPLITS == 0 ? 1 : SPLITS == 1 ? p.n_split : (p.n_split + 1) >> 1;  // waves of the workgroup
   const int g = lane >> 4, c = lane & 15;
   const int L = p.L;
-  // Workgroup -> (head, row group), so that the workgroups an XCD (block index mod
-  // 8) runs together share few heads' K and V through its L2.  BH up to 8 or a
-  // multiple of 8: heads fastest, then the row groups that see the most keys
-  // first (causal).  Else XCD x takes the x-th eighth of the workgroups in
-  // head-major order.
-  const int n_rg = (L + R - 1) / R, total = p.BH * n_rg;
+  // Workgroup -> (head, row group), so that the workgroups an XCD (linear block
+  // index mod 8) runs together share few heads' K and V through its L2, and the
+  // row groups that see the most keys come first (causal).  Fewer than 8 heads, or
+  // a multiple of 8: heads fastest within a row group, eight heads at a time, from
+  // the grid's dimensions (a division here costs 0.5 us of cold instructions).
+  // Else XCD x takes the x-th eighth of the workgroups in head-major order, which
+  // keeps the XCDs level.  (With all heads fastest, 1024 heads at L = 512 read each
+  // head's K and V from memory once per row group: 634 us instead of 249.)
   int head, rank;
-  if (p.BH <= 8 || p.BH % 8 == 0) {
-    head = blockIdx.x % p.BH;
-    rank = blockIdx.x / p.BH;
+  const int n_rg = (L + R - 1) / R;
+  if (short_grid_by_head(p.BH)) {
+    head = blockIdx.z * 8 + blockIdx.x;
+    rank = blockIdx.y;
   } else {
-    const int t = (int)(blockIdx.x % 8) * ((total + 7) / 8) + (int)(blockIdx.x / 8);
+    const int t = (int)(blockIdx.x % 8) * (int)(gridDim.x / 8) + (int)(blockIdx.x / 8);
     head = t / n_rg;
     rank = t - head * n_rg;
+    if (head >= p.BH) return;
   }
-  if (head >= p.BH || rank >= n_rg) return;  // the grid is a multiple of 8
   const int rg = p.causal ? n_rg - 1 - rank : rank;
   const int r0 = rg * R;
   const size_t hoff = (size_t)head * (size_t)L * D;
@@ -311,19 +322,29 @@ __global__ void __launch_bounds__(512) short_kernel(const FwdParams p) {
         const int ch = (2 * db + (g >> 1)) ^ k_swz<KCH>(r);
         *(ATTN_LDS u32x2_t*)(region + sp * R * ROWB + r * ROWB + ch * 16 + 8 * (g & 1)) = part[sp][qb][db];
       }
-      if (g == 0) {
+      if (SPLITS != 0 && g == 0) {
         ATTN_LDS float2* const e = ml + (w + sp * nw) * R + r;
         e->x = pm[sp][qb];
         e->y = pl[sp][qb];
       }
     }
-  __syncthreads();
-
-  // Merge: one (row, octet) item per thread and turn.
   constexpr int OCTS = D / 8;
+  // One split: the normalised rows are O itself.
+  if constexpr (SPLITS == 0) {
+#pragma unroll
+    for (int it = lane; it < R * OCTS; it += 64) {
+      const int r = it / OCTS, d8 = it - r * OCTS;
+      const u32x4_t v = *(ATTN_LDS const u32x4_t*)((ATTN_LDS char*)short_smem + r * ROWB + (d8 ^ k_swz<KCH>(r)) * 16);
+      if (r0 + r < L)
+        *reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(p.o) + hoff + (size_t)(r0 + r) * D + 8 * d8) = v;
+    }
+    return;
+  }
+  __syncthreads();
+  // Merge: one (row, octet) item per thread and turn.
   auto merge = [&](auto nsc) ATTN_INLINE {
     constexpr int NS = decltype(nsc)::value;
-    for (int it = tid; it < R * OCTS; it += blockDim.x) {
+    for (int it = tid; it < R * OCTS; it += 64 * nw) {
       const int r = it / OCTS, d8 = it - r * OCTS, q = r0 + r;
       if (q >= L) continue;
       int n = p.n_split;
@@ -339,7 +360,7 @@ __global__ void __launch_bounds__(512) short_kernel(const FwdParams p) {
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         const int sc = min(s, n - 1);
-        const int slot = SPW == 1 ? 0 : sc / nw, reg = SPW == 1 ? sc : sc % nw;
+        const int slot = SPLITS == 1 ? 0 : sc / nw, reg = SPLITS == 1 ? sc : sc % nw;
         st[s].x = ml[sc * R + r].x;
         st[s].y = ml[sc * R + r].y;
         po[s] = *(ATTN_LDS const u32x4_t*)((ATTN_LDS char*)short_smem + reg * kShortRegion + slot * R * ROWB + r * ROWB +
@@ -349,37 +370,44 @@ __global__ void __launch_bounds__(512) short_kernel(const FwdParams p) {
           merge_splits<DT, NS>(st, po, n);
     }
   };
-  if constexpr (SPW == 2) merge(std::integral_constant<int, 16>{});
+  if constexpr (SPLITS == 2) merge(std::integral_constant<int, 16>{});
   else if (p.n_split <= 2) merge(std::integral_constant<int, 2>{});
   else if (p.n_split <= 4) merge(std::integral_constant<int, 4>{});
   else merge(std::integral_constant<int, 8>{});
 #endif
 }
 
-template <int DT, int D, int TKV, int QB, int SPW>
+template <int DT, int D, int TKV, int QB, int SPLITS>
 hipError_t launch_short_i(const FwdParams& p, hipStream_t s) {
-  const int nw = (p.n_split + SPW - 1) / SPW;
-  const unsigned lds = nw * kShortRegion + p.n_split * 16 * QB * (unsigned)sizeof(float2) + (SPW == 2 ? 128 : 0);
-  const int64_t grid = ((int64_t)p.BH * ((p.L + 16 * QB - 1) / (16 * QB)) + 7) / 8 * 8;
-  if (p.n_split < 1 || nw > 8 || grid > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((short_kernel<DT, D, TKV, QB, SPW>), dim3((unsigned)grid), dim3(64 * nw), lds, s, p);
+  const int nw = SPLITS == 0 ? 1 : (p.n_split + SPLITS - 1) / SPLITS;
+  const unsigned lds = nw * kShortRegion + (SPLITS == 0 ? 0 : SPLITS * nw * 16 * QB * (unsigned)sizeof(float2));
+  const int64_t n_rg = (p.L + 16 * QB - 1) / (16 * QB), total = p.BH * n_rg;
+  if (p.n_split < 1 || nw > 8 || n_rg > 65535 || total > 0x7ffffff0) return hipErrorInvalidValue;
+  const dim3 grid = short_grid_by_head(p.BH) ? dim3(p.BH < 8 ? p.BH : 8, (unsigned)n_rg, (p.BH + 7) / 8)
+                                             : dim3((unsigned)((total + 7) / 8 * 8));
+  hipLaunchKernelGGL((short_kernel<DT, D, TKV, QB, SPLITS>), grid, dim3(64 * nw), lds, s, p);
   return hipGetLastError();
+}
+
+template <int DT, int D, int TKV, int QB>
+hipError_t launch_short_q(const FwdParams& p, hipStream_t s) {
+  if (p.n_split == 1) return launch_short_i<DT, D, TKV, QB, 0>(p, s);
+  if (p.n_split <= 8) return launch_short_i<DT, D, TKV, QB, 1>(p, s);
+  if constexpr (QB == 1) return launch_short_i<DT, D, TKV, QB, 2>(p, s);
+  else return hipErrorInvalidValue;  // two splits per wave with 16 rows only
 }
 
 template <int DT>
 hipError_t launch_short_t(const FwdParams& p, int d, int rows, hipStream_t s) {
-  const bool two = p.n_split > 8;
-  if (d == 256) return two ? launch_short_i<DT, 256, 32, 1, 2>(p, s) : launch_short_i<DT, 256, 32, 1, 1>(p, s);
-  if (d == 128) {
-    if (two) return launch_short_i<DT, 128, 64, 1, 2>(p, s);
-    return rows == 32 ? launch_short_i<DT, 128, 64, 2, 1>(p, s) : launch_short_i<DT, 128, 64, 1, 1>(p, s);
+  if (d == 256) return launch_short_q<DT, 256, 32, 1>(p, s);
+  if (rows == 32) {
+    if (d == 128) return launch_short_q<DT, 128, 64, 2>(p, s);
+    if (d == 96) return launch_short_q<DT, 96, 64, 2>(p, s);
+    return launch_short_q<DT, 64, 128, 2>(p, s);
   }
-  if (d == 96) {
-    if (two) return launch_short_i<DT, 96, 64, 1, 2>(p, s);
-    return rows == 32 ? launch_short_i<DT, 96, 64, 2, 1>(p, s) : launch_short_i<DT, 96, 64, 1, 1>(p, s);
-  }
-  if (two) return launch_short_i<DT, 64, 128, 1, 2>(p, s);
-  return rows == 32 ? launch_short_i<DT, 64, 128, 2, 1>(p, s) : launch_short_i<DT, 64, 128, 1, 1>(p, s);
+  if (d == 128) return launch_short_q<DT, 128, 64, 1>(p, s);
+  if (d == 96) return launch_short_q<DT, 96, 64, 1>(p, s);
+  return launch_short_q<DT, 64, 128, 1>(p, s);
 }
 
 }  // namespace attn

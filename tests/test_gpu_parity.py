@@ -703,10 +703,32 @@ def test_rows_past_the_sequence_are_not_written(L, d, dtype):
         assert (buf[:2048] == 3).all() and (buf[2048 + n:] == 3).all()
 
 
+def _short_rows_unsplit(r, BH, L, d, causal):
+    n_kv = -(-L // r.t_kv)
+    if (r.n_waves == 1 and r.grid <= 256) or n_kv > 32:
+        return 0
+
+    def seen(rows):
+        return [min(n_kv, -(-min(L, (i + 1) * rows) // r.t_kv)) if causal else n_kv for i in range(-(-L // rows))]
+
+    q = seen(r.tile_q)
+    step = {64: 1.9, 256: 1.0}.get(d, 1.6)
+    best = (0.8 if d == 256 else 0.95) * (2 + -(-r.grid // 256) * (7 + step * sum(q) / len(q)))
+    pick = 0
+    for rows, wg, tile, chain in ((32, 0.6, 0.35, 1.5), (16, 0.3, 0.35 if d == 256 else 0.26, 1.0)):
+        if rows == 32 and d == 256:
+            continue
+        w = seen(rows)
+        cost = max(4 + BH * (len(w) * wg + sum(w) * tile) / 256, 4.6 + chain * max(w))
+        if cost < best:
+            best, pick = cost, rows
+    return pick
+
+
 def _short_rows(r, BH, L, d, causal):
     """The short-sequence kernel's rule restated: rows per workgroup, or 0."""
-    if not 2 <= r.n_split <= 16:
-        return 0
+    if r.n_split == 1:
+        return _short_rows_unsplit(r, BH, L, d, causal)
     step = {64: 1.9, 256: 1.2}.get(d, 1.6)
     best = 0.95 * (4 + -(-r.grid // 256) * (8 + step * r.tiles_per_split) + (2 if causal else 0))
     per_wave = 2 if r.n_split > 8 else 1
@@ -730,6 +752,8 @@ SHORT = [
     (1, 8, 300, 128, False, "f16"), (1, 1, 697, 128, False, "bf16"), (3, 15, 129, 128, True, "bf16"),
     (1, 8, 1024, 64, False, "f16"), (1, 9, 257, 64, True, "bf16"), (1, 2, 1561, 64, True, "f16"), (1, 61, 511, 64, False, "bf16"),
     (1, 4, 1000, 96, False, "bf16"), (2, 5, 515, 96, True, "f16"), (1, 7, 112, 96, False, "f16"), (1, 60, 399, 96, False, "bf16"),
+    (1, 1000, 100, 128, False, "bf16"), (1, 300, 300, 128, True, "f16"), (1, 333, 64, 64, True, "bf16"), (1, 285, 271, 96, True, "f16"),
+    (1, 70, 352, 64, True, "bf16"), (1, 178, 66, 128, True, "f16"), (1, 334, 64, 256, False, "bf16"), (1, 300, 396, 64, False, "f16"), (1, 91, 64, 96, False, "bf16"),
     (1, 4, 1024, 256, False, "bf16"), (1, 9, 110, 256, True, "f16"), (1, 3, 500, 256, True, "bf16"), (1, 13, 65, 256, False, "f16"),
 ]
 
@@ -741,6 +765,8 @@ def test_short_sequence_cases_reach_every_instance():
         rows = _short_rows(r, B * H, L, d, causal)
         assert rows, (B, H, L, d)
         got.add((d, rows, 2 if r.n_split > 8 else 1))
+        got.add((d, rows, "unsplit" if r.n_split == 1 else "split"))
+    assert got >= {(d, r, "unsplit") for d, r in ((64, 16), (64, 32), (96, 32), (96, 16), (128, 16), (128, 32), (256, 16))}
     assert got >= {(d, r, s) for d in (64, 96, 128) for r, s in ((32, 1), (16, 1), (16, 2))} | {(256, 16, 1), (256, 16, 2)}
 
 
@@ -758,7 +784,8 @@ def test_short_sequence_kernel_equals_partial_and_merge(B, H, L, d, causal, dtyp
     buf = torch.full((n + 4096,), 3.0, dtype=tq.dtype, device="cuda")
     o = buf[2048:2048 + n].view(B, H, L, d)
     capi.attn_fwd(tq, tk, tv, o, s, causal)
-    ws = torch.empty(capi.attn_fwd_workspace_bytes(B, H, L, d, causal, dt), dtype=torch.uint8, device="cuda")
+    nb = capi.attn_fwd_workspace_bytes(B, H, L, d, causal, dt)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda") if nb else None
     two, na = torch.empty_like(tq), torch.empty_like(tq)
     capi.attn_fwd_partial(tq, tk, tv, two, s, causal, ws)
     capi.attn_fwd_merge(ws, two, s, causal)
