@@ -155,6 +155,32 @@ const GemmInstance* find_gemm(int dtype, bool qk, const attn_gemm_report_t& r) {
   return nullptr;
 }
 
+// attn_gemm's tile: the compiled one with the least estimated time, rounds of num_cus
+// tiles times (the fixed part of a tile + K times its measured time per k).
+// Halving a side until the tiles outnumber the CUs, as the derivation does,
+// often ends with a nearly empty second round of small tiles that read their
+// panels twice as often, where fewer, larger ones take one round: 305 x 2096 x
+// 4552 f16 330 tiles of 32 x 64 40.2 us, 165 of 64 x 64 25.0; 612 x 5144 x 1752 410 of 64
+// x 128 37.2, 205 of 128 x 128 23.6; 3000^3 288 of 128 x 256 92.0, 144 of 256 x 256
+// 68.0.  The fixed part (prologue and the C stores) is about 3 us for the 16-bit
+// tiles and 1 us for the fp32 ones, several of which share a CU.
+const GemmInstance* pick_gemm(int dtype, int64_t M, int64_t N, int64_t K, int num_cus) {
+  int n = 0;
+  const GemmInstance* table = dtype == ATTN_BF16 ? gemm_instances_bf16(&n)
+                              : dtype == ATTN_F16 ? gemm_instances_f16(&n)
+                                                  : gemm_instances_f32(&n);
+  const double fixed = dtype == ATTN_F32 ? 1.0 : 3.0;
+  const GemmInstance* best = nullptr;
+  double least = 0.0;
+  for (int i = 0; i < n; ++i) {
+    const int64_t tiles = ((M + table[i].t_m - 1) / table[i].t_m) * ((N + table[i].t_n - 1) / table[i].t_n);
+    if (tiles > 0x7fffff) continue;  // a launch takes fewer than 2^32 threads
+    const double cost = (double)((tiles + num_cus - 1) / num_cus) * (fixed + 1e-3 * K * table[i].ns_per_k);
+    if (!best || cost < least) best = &table[i], least = cost;
+  }
+  return best ? best : &table[0];
+}
+
 const FwdInstance* find_instance(int dtype, int d, int t_kv, int q_blocks, int n_waves) {
   using Fn = const FwdInstance* (*)(int*);
   Fn fns[] = {fwd_instances_bf16_d64, fwd_instances_bf16_d96, fwd_instances_bf16_d128, fwd_instances_bf16_d256,
@@ -713,15 +739,10 @@ int attn_gemm(const void* A, const void* B, float* C, int64_t M, int64_t N, int6
   if (rc != ATTN_OK) return rc;
   const int64_t n_tm = (M + rep.t_m - 1) / rep.t_m, n_tn = (N + rep.t_n - 1) / rep.t_n;
   if (n_tm * n_tn > 0x7fffffffLL) return ATTN_E_SHAPE;
-  const GemmInstance* inst = nullptr;
-  int n = 0;
-  const GemmInstance* table = dtype == ATTN_BF16 ? gemm_instances_bf16(&n)
-                              : dtype == ATTN_F16 ? gemm_instances_f16(&n)
-                                                  : gemm_instances_f32(&n);
-  for (int i = 0; i < n; ++i)
-    if (table[i].t_m == rep.t_m && table[i].t_n == rep.t_n && table[i].t_k == rep.t_k) inst = &table[i];
+  const GemmInstance* inst = pick_gemm(dtype, M, N, K, desc.num_cus);
   if (!inst) return ATTN_E_NO_INSTANCE;
-  const GemmParams p{A, B, C, (int)M, (int)N, (int)K, (int)n_tm, (int)n_tn};
+  const int64_t tm = (M + inst->t_m - 1) / inst->t_m, tn = (N + inst->t_n - 1) / inst->t_n;
+  const GemmParams p{A, B, C, (int)M, (int)N, (int)K, (int)tm, (int)tn};
   return inst->launch(p, static_cast<hipStream_t>(stream)) == hipSuccess ? ATTN_OK : ATTN_E_HIP;
 }
 

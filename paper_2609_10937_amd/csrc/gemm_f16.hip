@@ -6,12 +6,12 @@
 namespace attn {
 
 static const GemmInstance kInstances[] = {
-    {ATTN_F16, 256, 256, 32, launch_gemm<ATTN_F16, 256, 256, 32, kGemmStages>},
-    {ATTN_F16, 128, 256, 32, launch_gemm<ATTN_F16, 128, 256, 32, kGemmStages>},
-    {ATTN_F16, 128, 128, 64, launch_gemm<ATTN_F16, 128, 128, 64, kGemmStages>},
-    {ATTN_F16, 64, 128, 64, launch_gemm<ATTN_F16, 64, 128, 64, kGemmStages>},
-    {ATTN_F16, 64, 64, 128, launch_gemm<ATTN_F16, 64, 64, 128, kGemmStages>},
-    {ATTN_F16, 32, 64, 128, launch_gemm<ATTN_F16, 32, 64, 128, kGemmStages>},
+    {ATTN_F16, 256, 256, 32, launch_gemm<ATTN_F16, 256, 256, 32, kGemmStages>, 24.f},
+    {ATTN_F16, 128, 256, 32, launch_gemm<ATTN_F16, 128, 256, 32, kGemmStages>, 15.5f},
+    {ATTN_F16, 128, 128, 64, launch_gemm<ATTN_F16, 128, 128, 64, kGemmStages>, 9.5f},
+    {ATTN_F16, 64, 128, 64, launch_gemm<ATTN_F16, 64, 128, 64, kGemmStages>, 6.1f},
+    {ATTN_F16, 64, 64, 128, launch_gemm<ATTN_F16, 64, 64, 128, kGemmStages>, 4.2f},
+    {ATTN_F16, 32, 64, 128, launch_gemm<ATTN_F16, 32, 64, 128, kGemmStages>, 2.5f},
 };
 
 const GemmInstance* gemm_instances_f16(int* n) {

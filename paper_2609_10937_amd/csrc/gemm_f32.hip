@@ -1,16 +1,22 @@
-// fp32 GEMM instances: the tiles the closed-form derivation yields on gfx950
-// for the fp32 kernel family (192 x 192 x 32 from LDS and registers; the CU
-// rule's halvings for smaller problems).
+// fp32 GEMM instances.  The derivation's tile (192 x 192 x 32 and its halvings,
+// one workgroup of one wave per SIMD per CU with all of LDS) leaves the matrix
+// cores waiting at every step's barrier and often runs nearly empty last rounds;
+// of these tiles all but the first fit two or three times on a CU, whose
+// workgroups fill each other's waits.  4096^3 1101 -> 967 us (128 x 128), 2999 x 2500
+// x 1500 222 -> 181 (192 x 160, one round of 256), 1024^3 40.8 -> 21.5.
 #include "gemm_f32_kernel.hpp"
 
 namespace attn {
 
+// ns_per_k: 2 t_m t_n over the 614 GFLOP/s of one CU, over the share of it that the
+// tile reaches (0.85, 0.89, 0.85, 0.86, 0.76, 0.60, measured at 20 to 4096 rows).
 static const GemmInstance kInstancesF32[] = {
-    {ATTN_F32, 192, 192, 32, launch_gemm_f32<192, 192, 32, kGemm32.stages>},
-    {ATTN_F32, 96, 192, 32, launch_gemm_f32<96, 192, 32, kGemm32.stages>},
-    {ATTN_F32, 96, 96, 64, launch_gemm_f32<96, 96, 64, kGemm32.stages>},
-    {ATTN_F32, 32, 96, 96, launch_gemm_f32<32, 96, 96, kGemm32.stages>},
-    {ATTN_F32, 32, 32, 192, launch_gemm_f32<32, 32, 192, kGemm32.stages>},
+    {ATTN_F32, 192, 160, 32, launch_gemm_f32<192, 160, 32, 3, 1>, 117.7f},
+    {ATTN_F32, 128, 128, 32, launch_gemm_f32<128, 128, 32, 2, 2>, 60.0f},
+    {ATTN_F32, 96, 96, 32, launch_gemm_f32<96, 96, 32, 3, 2>, 35.3f},
+    {ATTN_F32, 64, 64, 32, launch_gemm_f32<64, 64, 32, 3, 3>, 15.5f},
+    {ATTN_F32, 32, 64, 64, launch_gemm_f32<32, 64, 64, 3, 2>, 8.8f},
+    {ATTN_F32, 32, 32, 64, launch_gemm_f32<32, 32, 64, 3, 3>, 5.6f},
 };
 
 const GemmInstance* gemm_instances_f32(int* n) {

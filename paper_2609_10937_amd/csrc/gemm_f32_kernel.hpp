@@ -1,8 +1,7 @@
 // GEMM C = A B in fp32 for gfx950: Section 4's worked example in the type the
 // section measures it in, on v_mfma_f32_16x16x4_f32 (2048 flops in 32 cycles),
-// with the workgroup tile t_M x t_N x t_K and the per-wave tile from the
-// closed-form derivation for this kernel family's structure (3 LDS stages,
-// 2 x 2 waves, one per SIMD).
+// with the workgroup tile t_M x t_N x t_K, ST LDS stages and 2 x 2 waves, OCC
+// workgroups to a CU (one wave per SIMD each).
 //
 // As in the 16-bit kernel the product is formed as C^T = B^T A^T, so a lane's
 // result fragment is four consecutive columns of one row of C.  Fragment
@@ -47,8 +46,8 @@ __device__ __forceinline__ int f32_b_swz(int r) {
   else return 4 * ((r >> 2) & 1);
 }
 
-template <int TM, int TN, int TK, int ST>
-__global__ void __launch_bounds__(256) matmul_f32_kernel(const GemmParams p) {
+template <int TM, int TN, int TK, int ST, int OCC>
+__global__ void __launch_bounds__(256, OCC) matmul_f32_kernel(const GemmParams p) {
   constexpr int WM = kGemm32.waves_m, WN = kGemm32.waves_n, NW = WM * WN;
   static_assert(NW == 4, "four waves");
   constexpr int WTM = TM / WM, WTN = TN / WN;   // per-wave tile of C
@@ -227,10 +226,10 @@ __global__ void __launch_bounds__(256) matmul_f32_kernel(const GemmParams p) {
   }
 }
 
-template <int TM, int TN, int TK, int ST>
+template <int TM, int TN, int TK, int ST, int OCC>
 hipError_t launch_gemm_f32(const GemmParams& p, hipStream_t s) {
   const unsigned grid = (unsigned)p.n_tm * (unsigned)p.n_tn;
-  hipLaunchKernelGGL((matmul_f32_kernel<TM, TN, TK, ST>), dim3(grid), dim3(256), 0, s, p);
+  hipLaunchKernelGGL((matmul_f32_kernel<TM, TN, TK, ST, OCC>), dim3(grid), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 

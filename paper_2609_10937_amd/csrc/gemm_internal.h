@@ -32,6 +32,7 @@ struct GemmInstance {
   int dtype;
   int t_m, t_n, t_k;
   GemmLaunch launch;
+  float ns_per_k = 0.f;  // measured time of one k position of a tile, a tile per CU (attn_gemm's choice)
 };
 
 const GemmInstance* gemm_instances_bf16(int* n);
