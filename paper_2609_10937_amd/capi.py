@@ -106,11 +106,38 @@ class AttnError(RuntimeError):
 
 
 _lib = None
+# The native calls of _torch_call.so (csrc/torch_call.cpp) for the entry points that
+# a program calls per launch, bound by load(); None where the module or torch's
+# stream getter is missing, and the calls then marshal through ctypes.  A native
+# call returns the entry's status, or None for arguments that it leaves to the
+# checks here.
+_native = None
+_TORCH_CALL_PATH = os.path.join(HERE, "_torch_call.so")
+
+
+def _bind_native(lib):
+    if not os.path.exists(_TORCH_CALL_PATH):
+        return None
+    try:
+        import importlib.util
+
+        import torch
+        getter = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if getter is None:
+            return None
+        spec = importlib.util.spec_from_file_location("paper_2609_10937_amd._torch_call", _TORCH_CALL_PATH)
+        native = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(native)
+    except ImportError:
+        return None
+    native.bind(*(ctypes.cast(f, c_void_p).value
+                  for f in (lib.attn_fwd, lib.attn_fwd_noalloc, lib.attn_softmax, lib.attn_gemm)), getter)
+    return native
 
 
 def load():
     """Load libattn.so (no GPU access).  Raises if it has not been built."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -157,6 +184,7 @@ def load():
         fn = getattr(lib, name)
         fn.restype = res
         fn.argtypes = args
+    _native = _bind_native(lib)
     _lib = lib
     return lib
 
@@ -165,6 +193,11 @@ def _check(rc):
     if rc != 0:
         raise AttnError(rc, load().attn_strerror(rc).decode())
     return rc
+
+
+def _done(rc):
+    if rc != 0:
+        _check(rc)
 
 
 # ------------------------------------------------------------ host-side calls
@@ -276,6 +309,10 @@ def _same(q, k, v, o):
 
 def attn_fwd(q, k, v, o, scale: float, causal: bool, stream=None):
     """Enqueue the fused forward on `stream` (default: torch's current stream)."""
+    if stream is None and _native is not None:
+        rc = _native.attn_fwd(q, k, v, o, scale, causal)
+        if rc is not None:
+            return _done(rc)
     B, H, L, d = q.shape
     _same(q, k, v, o)
     _check(load().attn_fwd(_dev_ptr(q), _dev_ptr(k), _dev_ptr(v), _dev_ptr(o), B, H, L, d,
@@ -285,6 +322,10 @@ def attn_fwd(q, k, v, o, scale: float, causal: bool, stream=None):
 def attn_fwd_noalloc(q, k, v, o, scale: float, causal: bool, stream=None):
     """attn_fwd with the split workspace in the library's static per-GPU array
     (no allocation; calls that overlap on one GPU race on it)."""
+    if stream is None and _native is not None:
+        rc = _native.attn_fwd_noalloc(q, k, v, o, scale, causal)
+        if rc is not None:
+            return _done(rc)
     B, H, L, d = q.shape
     _same(q, k, v, o)
     _check(load().attn_fwd_noalloc(_dev_ptr(q), _dev_ptr(k), _dev_ptr(v), _dev_ptr(o), B, H, L, d,
@@ -340,6 +381,10 @@ def attn_softmax_derive(hw: HwDesc, rows: int, n: int, elem_bytes: int = 2) -> S
 
 def attn_softmax(x, y, causal: bool = False, stream=None):
     """y = softmax(x) along the last dimension (x, y contiguous, same shape and dtype; y may be x)."""
+    if stream is None and _native is not None:
+        rc = _native.attn_softmax(x, y, causal)
+        if rc is not None:
+            return _done(rc)
     if tuple(y.shape) != tuple(x.shape) or y.dtype != x.dtype:
         raise AttnError(CODE["ATTN_E_SHAPE"], "x and y must share shape and dtype")
     n = x.shape[-1]
@@ -357,6 +402,10 @@ def attn_gemm_derive(hw: HwDesc, atom: Atom, M: int, N: int, K: int) -> GemmRepo
 def attn_gemm(a, b, c, stream=None):
     """c = a @ b: a [M, K] and b [K, N] contiguous device tensors of one dtype
     (bf16, f16 or float32), c [M, N] contiguous float32."""
+    if stream is None and _native is not None:
+        rc = _native.attn_gemm(a, b, c)
+        if rc is not None:
+            return _done(rc)
     import torch
     if a.dim() != 2 or b.dim() != 2 or c.dim() != 2:
         raise AttnError(CODE["ATTN_E_SHAPE"], "a, b and c must be matrices")

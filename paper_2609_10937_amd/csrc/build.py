@@ -1,4 +1,5 @@
-"""Build libattn.so (HIP kernels + C ABI) for gfx950 with hipcc.
+"""Build libattn.so (HIP kernels + C ABI) for gfx950 with hipcc, and the Python
+module _torch_call.so that hands torch tensors to it.
 
 Every translation unit is compiled in parallel into _build/ at the repository
 root and linked into paper_2609_10937_amd/libattn.so.  The compiler's
@@ -20,6 +21,7 @@ PKG = os.path.dirname(HERE)
 ROOT = os.path.dirname(PKG)
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libattn.so")
+TORCH_CALL = os.path.join(PKG, "_torch_call.so")
 
 SOURCES = [
     "capi.cpp",
@@ -107,17 +109,37 @@ def _parse_resources(text):
     return out
 
 
+def _build_torch_call():
+    """The Python module of torch_call.cpp (host code only, on torch's headers)."""
+    import sysconfig
+
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    tmp = TORCH_CALL + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(tdir, "include"), "-I", os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], os.path.join(HERE, "torch_call.cpp"), "-o", tmp,
+           "-L", os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stderr}")
+    os.replace(tmp, TORCH_CALL)
+
+
 def build(jobs: int | None = None, verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     jobs = jobs or min(8, len(SOURCES), os.cpu_count() or 1)
     resources = {}
     objs = []
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
+        torch_call = ex.submit(_build_torch_call)
         for obj, err in ex.map(_compile, SOURCES):
             objs.append(obj)
             resources.update(_parse_resources(err))
             if verbose:
                 print(f"built {os.path.basename(obj)}", flush=True)
+        torch_call.result()
     tmp = LIB + ".tmp"
     cmd = [_hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -1,0 +1,116 @@
+"""The native calls that take torch tensors straight to the C entries
+(csrc/torch_call.cpp): they accept only the plain case, everything else returns
+None and goes through the Python checks, so results and errors are those of the
+ctypes path."""
+import numpy as np
+import pytest
+
+from paper_2609_10937_amd import capi, inputs
+
+torch = pytest.importorskip("torch")
+
+
+class Sub(torch.Tensor):
+    pass
+
+
+def test_module_is_built_and_bound():
+    capi.load()
+    assert capi._native is not None
+
+
+def test_cpu_tensors_and_odd_arguments_are_left_to_python():
+    capi.load()
+    n = capi._native
+    x = torch.zeros((2, 8), dtype=torch.bfloat16)
+    q = torch.zeros((1, 1, 16, 64), dtype=torch.bfloat16)
+    assert n.attn_softmax(x, x, False) is None
+    assert n.attn_softmax(x, x, 2) is None and n.attn_softmax(x, None, True) is None and n.attn_softmax(x, x) is None
+    assert n.attn_gemm(x, x, x) is None and n.attn_gemm(1, 2, 3) is None
+    assert n.attn_fwd(q, q, q, q, 1.0, False) is None
+    assert n.attn_fwd(q, q, q, q, 1, False) is None and n.attn_fwd(q, q, q, q, 1.0, "no") is None
+    assert n.attn_fwd_noalloc(q, q, q, q.as_subclass(Sub), 1.0, True) is None
+    with pytest.raises(TypeError):
+        n.bind(1, 2)
+    with pytest.raises(capi.AttnError) as e:
+        capi.attn_fwd(q, q, q, q, 1.0, False)
+    assert e.value.status == capi.CODE["ATTN_E_ARG"]
+
+
+def _both(monkeypatch, call):
+    """call() through the native module and through ctypes: the value or the AttnError status of each."""
+    out = []
+    for native in (capi._native, None):
+        with monkeypatch.context() as m:
+            m.setattr(capi, "_native", native)
+            try:
+                out.append(call())
+            except capi.AttnError as e:
+                out.append(e.status)
+            torch.cuda.synchronize()
+    return out
+
+
+@pytest.mark.gpu
+def test_native_and_ctypes_calls_agree(monkeypatch):
+    """Valid calls on two streams, strided, subclassed, mistyped and misshapen
+    tensors, arguments of other types: the same outputs or the same status."""
+    print("case torch_call", flush=True)
+    capi.load()
+    assert capi._native is not None
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+
+    def rnd(shape, dt):
+        return torch.randn(shape, generator=g, device="cuda").to(dt)
+
+    for dt in (torch.bfloat16, torch.float16):
+        q, k, v = (rnd((2, 3, 200, 64), dt) for _ in range(3))
+        for fn in (capi.attn_fwd, capi.attn_fwd_noalloc):
+            for scale, causal in ((0.125, True), (0.125, False), (1, 0), (np.float32(0.5), 1), (0.125, np.bool_(True))):
+                def call():
+                    o = torch.full_like(q, float("nan"))
+                    side = torch.cuda.Stream()
+                    side.wait_stream(torch.cuda.current_stream())
+                    with torch.cuda.stream(side):
+                        fn(q, k, v, o, scale, causal)
+                    torch.cuda.synchronize()
+                    return o
+                a, b = _both(monkeypatch, call)
+                assert torch.equal(a.view(torch.int16), b.view(torch.int16)) and torch.isfinite(a.float()).all()
+        o = torch.empty_like(q)
+        t = q.transpose(1, 2)
+        bad = [(t, t, t, t, 0.1, False), (q, k, v, o[:, :, :100], 0.1, False), (q, k, v.float(), o, 0.1, False),
+               (q, k, v, o, -1.0, False), (q, k, v, o, float("nan"), True), (q[..., :32].contiguous(),) * 4 + (0.1, False),
+               (q.cpu(), k, v, o, 0.1, False), (q.float(), k.float(), v.float(), o.float(), 0.1, False)]
+        for args in bad:
+            a, b = _both(monkeypatch, lambda: capi.attn_fwd(*args))
+            assert isinstance(a, int) and a == b, args
+        a, b = _both(monkeypatch, lambda: capi.attn_fwd(q.as_subclass(Sub), k, v, o, 0.1, False))
+        assert a is None and b is None
+
+        x = rnd((7, 33), dt)
+        a, b = _both(monkeypatch, lambda: (lambda y: (capi.attn_softmax(x, y), y)[1])(torch.empty_like(x)))
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+        for args in ((x, x[:5]), (x, x.t().contiguous()), (x.t(), x.t()), (x, x.float()), (x[:, :0], x[:, :0])):
+            a, b = _both(monkeypatch, lambda: capi.attn_softmax(*args))
+            assert isinstance(a, int) and a == b
+        m, w = rnd((40, 64), dt), rnd((64, 48), dt)
+        a, b = _both(monkeypatch, lambda: (lambda c: (capi.attn_gemm(m, w, c), c)[1])(torch.empty((40, 48), device="cuda")))
+        assert torch.equal(a, b)
+        c = torch.empty((40, 48), device="cuda")
+        for args in ((m, w, c.to(dt)), (m, w.float(), c), (m, w.t(), c), (m, m, c), (m[:, :60], w[:60], c), (m, w, c.t()),
+                     (m[:, :60].contiguous(), w[:60].contiguous(), c), (m.cpu(), w, c)):
+            a, b = _both(monkeypatch, lambda: capi.attn_gemm(*args))
+            assert isinstance(a, int) and a == b, args
+    s = inputs.softmax_scale(64)
+    q = rnd((1, 1, 64, 64), torch.bfloat16)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    outs = []
+    for stream in (None, side, side.cuda_stream):
+        o = torch.empty_like(q)
+        capi.attn_fwd(q, q, q, o, s, False, stream=stream)
+        torch.cuda.synchronize()
+        outs.append(o)
+    assert all(torch.equal(outs[0].view(torch.int16), o.view(torch.int16)) for o in outs)
