@@ -831,22 +831,48 @@ __global__ void __launch_bounds__(NW * 64) fwd_kernel(const FwdParams p) {
       }
     }
   };
-  // PERSIST: the current unit's rows (no split), through a buffer descriptor
-  // over its head's O, so rows past the sequence are dropped by the
-  // descriptor's range and every wave issues exactly QB * NDB stores (the
-  // waits of the unit switch count them).
-  [[maybe_unused]] auto store_unit_rows = [&]() ATTN_INLINE {
+  // PERSIST: the finished unit's rows (no split) after M(J), J the tile after its
+  // last.  At d = 128 they pass through LDS like store_block's, 16 rows x 128 bytes
+  // at a time, so that a store writes whole 128-byte segments instead of 32 bytes
+  // of 16 rows (1024 heads at L = 512 170.6 -> 162.5 us, 300 heads at L = 700 92.2 ->
+  // 90.1; at d = 64, with half the bytes per row, 160.9 -> 162.2, so not there).
+  // The wave's 2 KB lie in the K part of tile J - 1's stage: every wave had read
+  // that K tile before the barrier before M(J), and the next copies into the stage
+  // are requested after the barrier that follows.  The buffer descriptor over the
+  // head's O drops rows past the sequence, and every wave issues the same number
+  // of stores (the waits of the unit switch count them).
+  constexpr bool PROWS = PERSIST && D == 128;
+  static_assert(!PROWS || NW * 2048 <= TILEB, "row staging");
+  [[maybe_unused]] auto store_unit_rows = [&](int J) ATTN_INLINE {
     const __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc(
         reinterpret_cast<void*>(uniform_ptr(static_cast<uint16_t*>(p.o) + hoff)), (short)0,
         __builtin_amdgcn_readfirstlane((int)((uint32_t)L * (uint32_t)(D * 2))), 0x00020000);
+    ATTN_LDS char* const buf = lds + __builtin_amdgcn_readfirstlane(((J + ST - 1) % ST) * STAGEB + w * 2048);
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       const float lt = lacc[qb][0];
       const float inv = lt > 0.f ? 1.f / lt : 0.f;
-      const uint32_t rowb = (uint32_t)(q0 + 16 * qb + c) * (uint32_t)(D * 2) + 8u * (uint32_t)g;
+      if constexpr (PROWS) {
 #pragma unroll
-      for (int db = 0; db < NDB; ++db)
-        __builtin_amdgcn_raw_buffer_store_b64(pack4(o[qb][db] * inv), ors, (int)(rowb + 32u * (uint32_t)db), 0, 0);
+        for (int hp = 0; hp < D / 64; ++hp) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            *(ATTN_LDS u32x2_t*)(buf + c * 128 + ((2 * i + (g >> 1)) ^ k_swz<8>(c)) * 16 + 8 * (g & 1)) =
+                pack4(o[qb][4 * hp + i] * inv);
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const int r = 8 * i + lane / 8, ch = lane % 8;
+            const u32x4_t v = *(ATTN_LDS const u32x4_t*)(buf + r * 128 + (ch ^ k_swz<8>(r)) * 16);
+            __builtin_amdgcn_raw_buffer_store_b128(
+                v, ors, (int)((uint32_t)(q0 + 16 * qb + r) * (uint32_t)(D * 2) + (uint32_t)(128 * hp + 16 * ch)), 0, 0);
+          }
+        }
+      } else {
+        const uint32_t rowb = (uint32_t)(q0 + 16 * qb + c) * (uint32_t)(D * 2) + 8u * (uint32_t)g;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+          __builtin_amdgcn_raw_buffer_store_b64(pack4(o[qb][db] * inv), ors, (int)(rowb + 32u * (uint32_t)db), 0, 0);
+      }
     }
   };
 
@@ -903,7 +929,7 @@ __global__ void __launch_bounds__(NW * 64) fwd_kernel(const FwdParams p) {
       // tiles (the host checks), so the copies and the Q rows in flight
       // belong to the current or the next unit only.
       static_assert(AHEAD == 2, "the switch's waits assume two tiles requested ahead");
-      constexpr int NST = QB * NDB;  // store instructions of a unit's rows, per wave
+      constexpr int NST = PROWS ? QB * D / 32 : QB * NDB;  // store instructions of a unit's rows, per wave
       constexpr int QL = QB * KC;    // load instructions of a unit's Q rows, per wave
       static_assert(4 * LPW + NST + QL < 64, "vmcnt range");
       int r = 0;  // round of the current unit
@@ -980,7 +1006,7 @@ __global__ void __launch_bounds__(NW * 64) fwd_kernel(const FwdParams p) {
         }
         matrix(yes, yes, j, qf);
         if (sw_now) {
-          store_unit_rows();
+          store_unit_rows(j);
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int qb = 0; qb < QB; ++qb) {
@@ -1017,7 +1043,7 @@ __global__ void __launch_bounds__(NW * 64) fwd_kernel(const FwdParams p) {
   }
 
   if constexpr (PERSIST) {
-    store_unit_rows();
+    store_unit_rows(cur_end);
   } else {
     const size_t prow = ((size_t)split * p.BH + head) * (size_t)L + q0;  // row q0 of the split's partials
     uint16_t* const dst = p.n_split == 1 ? static_cast<uint16_t*>(p.o) + hoff + (size_t)q0 * D

@@ -189,3 +189,15 @@ def test_replay_catches_a_short_wait():
         _replay_waits([4, 5, 4], lpw=2, ql=8, nst=16, allow=(8, 17))
     with pytest.raises(AssertionError):
         _replay_waits([5, 6, 4], lpw=2, ql=8, nst=16, allow=(9, 16))
+
+
+@pytest.mark.parametrize("units", [[4, 4, 4, 4], [4, 5, 4], [8] * 8, [5, 6, 4, 12], [64, 4, 60, 8]])
+def test_waits_with_whole_row_stores(units):
+    """At d = 128 a finished query tile leaves as 16-byte stores of whole row
+    segments through LDS, 8 per wave instead of 16 (two blocks of 16 rows, two
+    halves of 128 bytes, two stores each): the wait rule with that count holds,
+    and one that counted a store too many would not."""
+    checks, conservative = _replay_waits(units, lpw=2, ql=8, nst=8)
+    assert checks > 0 and all(min(a, b) == 4 for _, a, b in conservative)
+    with pytest.raises(AssertionError):
+        _replay_waits(units, lpw=2, ql=8, nst=8, allow=(8, 9))
