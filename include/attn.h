@@ -338,7 +338,9 @@ int attn_gemm_derive(const attn_hw_desc_t* hw, const attn_mfma_atom_t* atom, int
  * 16x16x32 atom (products exact in fp32), fp32 inputs (ATTN_F32, the section's own
  * type) on the 16x16x4 fp32 atom.  The tile is the compiled one with the least
  * estimated time for the shape: for bf16/f16 one that attn_gemm_derive reaches
- * for some shape on gfx950, for fp32 one of a set that also shares CUs.
+ * for some shape on gfx950, or for few tiles and a long K a 32 x 32 tile whose waves
+ * split K (partial sums added in a fixed order); for fp32 one of a set that also
+ * shares CUs.
  * Sizes: 1 <= M < 2^31; N and K multiples of 8 (bf16/f16) or 4 (fp32), at
  * least that, K <= 2^22 and N <= 2^24 (bf16/f16) or 2^22 (fp32)
  * (ATTN_E_SHAPE otherwise); A, B and C 16-byte aligned (ATTN_E_ALIGN).  C

@@ -175,6 +175,10 @@ const GemmInstance* pick_gemm(int dtype, int64_t M, int64_t N, int64_t K, int nu
   for (int i = 0; i < n; ++i) {
     const int64_t tiles = ((M + table[i].t_m - 1) / table[i].t_m) * ((N + table[i].t_n - 1) / table[i].t_n);
     if (tiles > 0x7fffff) continue;  // a launch takes fewer than 2^32 threads
+    // The tile whose waves split K (32 x 32, 16-bit inputs): in one round only, and
+    // not for rows of A a multiple of 4 KB apart, whose 64-byte segments meet on one
+    // memory channel (512 x 512 x 4096 11.7 us with a barrier per step, 12.8 split).
+    if (dtype != ATTN_F32 && table[i].t_n == 32 && (tiles > num_cus || K % 2048 == 0)) continue;
     const double cost = (double)((tiles + num_cus - 1) / num_cus) * (fixed + 1e-3 * K * table[i].ns_per_k);
     if (!best || cost < least) best = &table[i], least = cost;
   }

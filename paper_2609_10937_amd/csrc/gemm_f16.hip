@@ -1,7 +1,8 @@
 // GEMM instances for f16 inputs: the tiles the closed-form derivation yields
 // on gfx950 (256 x 256 x 32 from LDS and registers; the CU rule's halvings
-// for small problems).
-#include "gemm_kernel.hpp"
+// for small problems), and the tile whose waves split K.  The last number is the
+// measured time of one k position in ns, a tile per CU.
+#include "gemm_ksplit_kernel.hpp"
 
 namespace attn {
 
@@ -12,6 +13,7 @@ static const GemmInstance kInstances[] = {
     {ATTN_F16, 64, 128, 64, launch_gemm<ATTN_F16, 64, 128, 64, kGemmStages>, 6.1f},
     {ATTN_F16, 64, 64, 128, launch_gemm<ATTN_F16, 64, 64, 128, kGemmStages>, 4.2f},
     {ATTN_F16, 32, 64, 128, launch_gemm<ATTN_F16, 32, 64, 128, kGemmStages>, 2.5f},
+    {ATTN_F16, kKsplitTile, kKsplitTile, kKsplitPiece, launch_gemm_ksplit<ATTN_F16>, 1.6f},
 };
 
 const GemmInstance* gemm_instances_f16(int* n) {

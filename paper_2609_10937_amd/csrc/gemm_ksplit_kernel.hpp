@@ -1,0 +1,150 @@
+// GEMM C = A B for few tiles and a long K (16-bit inputs): the waves of a
+// workgroup split K.
+//
+// A tile of 32 x 64 shared by eight waves gives each of them one product per 32
+// k positions between two barriers, so a skinny problem runs at the latency of
+// its steps, not at any rate of the chip.  Here every wave takes the whole 32 x
+// 32 tile of C for every eighth piece of 32 k positions: it copies its pieces of
+// A and B into LDS of its own (five slots, four pieces in flight), forms its
+// partial tile without a barrier, and the eight partial tiles are added in wave
+// order at the end, in fp32.  What bounds it is the L2's answer to 64-byte row
+// segments.  bf16, against the tiles with a barrier per step (us): 81 x 200 x 8024
+// 19.8 -> 11.7, 68 x 136 x 5720 14.9 -> 9.1, 31 x 864 x 6392 16.8 -> 9.4, 1 x 4104 x
+// 4104 14.3 -> 9.9.
+//
+// Fragments and products are the other GEMM kernel's (C^T = B^T A^T).  A piece is
+// A as two 1 KB blocks of 16 rows x 32 k in that kernel's block layout, and B as 32 rows of 64 bytes, whose 32-byte halves are
+// exchanged where bit 3 of the row is set, so that the transposing reads of two
+// 16-lane groups (rows 8 apart) fall on different banks.  Rows past M and k
+// positions past K arrive as zeros through the buffer descriptors; columns past N
+// hold data whose results are not stored.
+#pragma once
+
+#include "gemm_kernel.hpp"
+
+namespace attn {
+
+constexpr int kKsplitTile = 32, kKsplitPiece = 32, kKsplitWaves = 8, kKsplitSlots = 5;
+
+template <int DT>
+__global__ void __launch_bounds__(kKsplitWaves * 64) matmul_ksplit_kernel(const GemmParams p) {
+  using M_ = Mfma<DT>;
+  using V8 = typename M_::V8;
+  constexpr int T = kKsplitTile, KP = kKsplitPiece, NW = kKsplitWaves;
+  constexpr int SLOT = 4096, NS = kKsplitSlots, REGION = NS * SLOT;  // bytes of a piece, a wave
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[NW * REGION];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, c = lane & 15;
+  const int M = p.M, N = p.N, K = p.K;
+  // XCD x (block index mod 8) takes the x-th eighth of the tiles, along the shorter
+  // side of C fastest, so that the tiles that share the larger operand's rows or
+  // columns, and the halves of its memory lines, read them through one L2.
+  const int total = p.n_tm * p.n_tn, per = (total + 7) / 8;
+  const int t = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+  if (t >= total) return;
+  const bool cols = p.n_tm <= p.n_tn;
+  const int tm = cols ? t % p.n_tm : t / p.n_tn, tn = cols ? t / p.n_tm : t % p.n_tn;
+  const int m0 = tm * T, n0 = tn * T;
+  const int pieces = (K + KP - 1) / KP;
+  ATTN_LDS char* const lds = (ATTN_LDS char*)smem;
+  const uint32_t reg0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(size_t)(lds + w * REGION));
+
+  const uint32_t a_bytes = (uint32_t)min(M - m0, T) * (uint32_t)(K * 2);
+  const i32x4_t ars = buffer_rsrc(uniform_ptr(static_cast<const char*>(p.a) + (size_t)m0 * K * 2), a_bytes);
+  const uint64_t bbase = uniform_ptr(static_cast<const char*>(p.b) + (size_t)n0 * 2);
+  // A: slot l of a block is row 4 ((l / 4) % 4) + l / 16, chunk (l % 4) ^ (l / 16).
+  const int ar = (((lane >> 2) & 3) << 2) | (lane >> 4), ach = (lane & 3) ^ (lane >> 4);
+  // B: slot l of a copy of 16 rows is row l / 4, chunk (l % 4) ^ (2 (row / 8)).
+  const int br = lane >> 2, bch = (lane & 3) ^ (2 * ((br >> 3) & 1));
+  const uint32_t bcol = (uint32_t)min(n0 + 8 * bch, N - 8) - (uint32_t)n0;  // past N: the last chunk
+  auto copy_piece = [&](int piece, int slot) ATTN_INLINE {
+    const int k0 = min(piece * KP, K);  // a piece past the last is empty
+    // B rows of this piece that exist; the last row ends at column N.
+    const i32x4_t brs = buffer_rsrc(bbase + (uint64_t)k0 * N * 2,
+                                    k0 < K ? (uint32_t)min(K - k0, KP) * (uint32_t)(N * 2) - (uint32_t)(n0 * 2) : 0u);
+    const uint32_t dst = reg0 + (uint32_t)__builtin_amdgcn_readfirstlane(slot * SLOT);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int ka = k0 + 8 * ach;
+      const uint32_t off = ka < K ? (uint32_t)(16 * i + ar) * (uint32_t)(K * 2) + (uint32_t)(ka * 2) : a_bytes;
+      copy_to_lds_buf(ars, off, dst + i * 1024);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      copy_to_lds_buf(brs, (uint32_t)(16 * i + br) * (uint32_t)(N * 2) + bcol * 2, dst + 2048 + i * 1024);
+  };
+  const uint32_t la = reg0 + (uint32_t)(64 * (4 * (c & 3) + (c >> 2)) + 16 * (g ^ (c & 3)));
+  const int rb = 8 * g + (c >> 2);
+  const uint32_t lb = reg0 + 2048 + (uint32_t)(rb * 64 + 32 * ((rb >> 3) & 1) + 8 * (c & 3));
+
+  f32x4_t acc[2][2];  // [nb][mb]
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb) acc[nb][mb] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+
+  // The wave's pieces are w, w + NW, ...; pieces past the last are requested too, as
+  // empty copies, so that the waits count the same everywhere.
+#pragma unroll
+  for (int i = 0; i < NS - 1; ++i) copy_piece(w + i * NW, i);
+  int slot = 0;
+  for (int pc = w; pc < pieces; pc += NW) {
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vmcnt<4 * (NS - 2)>();
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t so = (uint32_t)__builtin_amdgcn_readfirstlane(slot * SLOT);
+    V8 fa[2], fb[2];
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+      fa[mb] = __builtin_bit_cast(
+          V8, *(ATTN_LDS const u32x4_t*)((ATTN_LDS const char*)(size_t)(la + so) + mb * 1024));
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      // Rows 8 g + c / 4 and 4 further down have the same bit 3.
+      ATTN_LDS const char* base = (ATTN_LDS const char*)(size_t)((lb ^ (uint32_t)(32 * nb)) + so);
+      const i16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ATTN_LDS i16x4_t*)base);
+      const i16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ATTN_LDS i16x4_t*)(base + 4 * 64));
+      const i16x8_t cat = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      fb[nb] = __builtin_bit_cast(V8, cat);
+    }
+    // The slot read in the last turn (its reads have returned: their products
+    // were issued) takes the piece NS - 1 turns ahead.
+    copy_piece(pc + (NS - 1) * NW, slot == 0 ? NS - 1 : slot - 1);
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb) acc[nb][mb] = M_::run(fb[nb], fa[mb], acc[nb][mb]);
+    slot = slot + 1 == NS ? 0 : slot + 1;
+  }
+  wait_vmcnt<0>();  // the empty copies too, before the region is used again
+
+  // Partial tiles to LDS, row-major [32][32] in 16-byte chunks swizzled per row,
+  // then their sum in wave order.
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+      *(ATTN_LDS f32x4_t*)(lds + w * REGION + (16 * mb + c) * 128 + (((4 * nb + g) ^ (c & 7)) * 16)) = acc[nb][mb];
+  __syncthreads();
+  if (tid < T * T / 4) {
+    const int r = tid >> 3, ch = tid & 7;
+    f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+      sum += *(ATTN_LDS const f32x4_t*)(lds + i * REGION + r * 128 + ((ch ^ (r & 7)) * 16));
+    const int m = m0 + r, n = n0 + 4 * ch;
+    if (m < M && n < N) *reinterpret_cast<f32x4_t*>(static_cast<float*>(p.c) + (size_t)m * N + n) = sum;
+  }
+}
+
+template <int DT>
+hipError_t launch_gemm_ksplit(const GemmParams& p, hipStream_t s) {
+  hipLaunchKernelGGL((matmul_ksplit_kernel<DT>), dim3(((unsigned)p.n_tm * (unsigned)p.n_tn + 7) / 8 * 8), dim3(kKsplitWaves * 64), 0, s, p);
+  return hipGetLastError();
+}
+
+}  // namespace attn
