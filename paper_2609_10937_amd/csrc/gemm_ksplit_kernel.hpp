@@ -9,15 +9,15 @@
 // partial tile without a barrier, and the eight partial tiles are added in wave
 // order at the end, in fp32.  What bounds it is the L2's answer to 64-byte row
 // segments.  bf16, against the tiles with a barrier per step (us): 81 x 200 x 8024
-// 19.8 -> 11.7, 68 x 136 x 5720 14.9 -> 9.1, 31 x 864 x 6392 16.8 -> 9.4, 1 x 4104 x
-// 4104 14.3 -> 9.9.
+// 19.6 -> 12.0, 68 x 136 x 5720 14.9 -> 9.2, 31 x 864 x 6392 16.9 -> 9.0, 1 x 4104 x
+// 4104 14.3 -> 9.9, 504 x 504 x 7000 (256 tiles) 23.7 -> 24.0.
 //
 // Fragments and products are the other GEMM kernel's (C^T = B^T A^T).  A piece is
-// A as two 1 KB blocks of 16 rows x 32 k in that kernel's block layout, and B as 32 rows of 64 bytes, whose 32-byte halves are
-// exchanged where bit 3 of the row is set, so that the transposing reads of two
-// 16-lane groups (rows 8 apart) fall on different banks.  Rows past M and k
-// positions past K arrive as zeros through the buffer descriptors; columns past N
-// hold data whose results are not stored.
+// A as two 1 KB blocks of 16 rows x 32 k in that kernel's block layout, and B as
+// 32 rows of 64 bytes, whose 32-byte halves are exchanged where bit 3 of the row is
+// set, so that the transposing reads of two 16-lane groups (rows 8 apart) fall on
+// different banks.  Rows past M and k positions past K arrive as zeros through
+// the buffer descriptors; columns past N hold data whose results are not stored.
 #pragma once
 
 #include "gemm_kernel.hpp"
@@ -143,7 +143,8 @@ __global__ void __launch_bounds__(kKsplitWaves * 64) matmul_ksplit_kernel(const 
 
 template <int DT>
 hipError_t launch_gemm_ksplit(const GemmParams& p, hipStream_t s) {
-  hipLaunchKernelGGL((matmul_ksplit_kernel<DT>), dim3(((unsigned)p.n_tm * (unsigned)p.n_tn + 7) / 8 * 8), dim3(kKsplitWaves * 64), 0, s, p);
+  hipLaunchKernelGGL((matmul_ksplit_kernel<DT>), dim3(((unsigned)p.n_tm * (unsigned)p.n_tn + 7) / 8 * 8),
+                     dim3(kKsplitWaves * 64), 0, s, p);
   return hipGetLastError();
 }
 
